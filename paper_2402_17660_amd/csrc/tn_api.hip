@@ -164,6 +164,13 @@ int parse_blob(const void *blob, size_t bytes, tn_model *m, std::vector<double> 
 }
 
 // ------------------------------------------------------------------ derived weight copies
+// The BF16 number nearest to a (not NaN) FP32 value, ties to even, on its bits: conversions of FP64 numbers
+// by the compiler may round in one step instead.
+__device__ __forceinline__ uint16_t bf16_bits(float v) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  return (uint16_t)((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
+}
+
 // The FP32 and BF16 copies of the packed FP64 weights.
 __global__ void k_weight_copies(int64_t n, const double *__restrict__ w, float *__restrict__ w32,
                                 __bf16 *__restrict__ w16) {
@@ -171,150 +178,75 @@ __global__ void k_weight_copies(int64_t n, const double *__restrict__ w, float *
   if (i >= n) return;
   const float v = (float)w[i];
   w32[i] = v;
-  // to nearest even on the bits of the FP32 value (finite), not in one step from FP64
-  const uint32_t b = __builtin_bit_cast(uint32_t, v);
-  w16[i] = __builtin_bit_cast(__bf16, (uint16_t)((b + 0x7fffu + ((b >> 16) & 1u)) >> 16));
+  w16[i] = __builtin_bit_cast(__bf16, bf16_bits(v));
 }
 
-// One matrix [ncol][kin] of the packed weights for the split kernels: its place in both buffers
-// and its scale.
+// One matrix [ncol][kin] of the packed weights for the FP32 path's products: its place in both buffers.
 struct SplitMat {
   int64_t src, dst;
   int32_t ncol, kin;
-  double scale;
 };
 
-// Hi/lo halves in fragment order (wave_mm_split): per column block and chunk of 32 along K (zeros
-// past kin and ncol), 64 lanes x 8 hi halves, then the lo halves.  One thread per lane of a block,
-// one matrix per blockIdx.y.
+// The three parts in fragment order (wave_mm_split): per column block and chunk of 32 along K (zeros
+// past kin and ncol), 64 lanes x 8 of the first part, of the second, of the third.  Each part is the
+// FP64 weight's remainder rounded to nearest on the bits of its FP32 value: to 2^-26 of the weight
+// together.  One thread per lane of a block, one matrix per blockIdx.y.
 __global__ void k_split_pack(const SplitMat *__restrict__ mats, const double *__restrict__ w,
-                             _Float16 *__restrict__ out) {
+                             __bf16 *__restrict__ out) {
   const SplitMat m = mats[blockIdx.y];
   const int32_t KC = (m.kin + 31) / 32, CB = (m.ncol + 15) / 16;
   const int32_t t = blockIdx.x * blockDim.x + threadIdx.x, lane = t & 63, blk = t >> 6;
   if (blk >= CB * KC) return;
   const int32_t c = blk / KC * 16 + lane % 16, k0 = blk % KC * 32 + 8 * (lane / 16);
-  _Float16 *p = out + m.dst + (int64_t)blk * 1024 + lane * 8;
+  __bf16 *p = out + m.dst + (int64_t)blk * 1536 + lane * 8;
   for (int j = 0; j < 8; ++j) {
-    const double x = c < m.ncol && k0 + j < m.kin ? w[m.src + (int64_t)c * m.kin + k0 + j] * m.scale : 0.0;
-    const _Float16 hi = (_Float16)(float)x;
-    p[j] = hi;
-    p[512 + j] = (_Float16)(float)(x - (double)(float)hi);
+    double x = c < m.ncol && k0 + j < m.kin ? w[m.src + (int64_t)c * m.kin + k0 + j] : 0.0;
+    for (int n = 0; n < 3; ++n) {
+      const uint16_t b = bf16_bits((float)x);
+      p[n * 512 + j] = __builtin_bit_cast(__bf16, b);
+      x -= (double)__builtin_bit_cast(float, (uint32_t)b << 16);
+    }
   }
 }
 
-// The exponent that brings values up to `bound` to at most 2^14.
-int split_exp(double bound) { return 14 - (int)std::ceil(std::log2(bound * 1.001)); }
-
-// Plans the split weights of a model the pair kernels cover, and their scales; returns the element
-// count of the split buffer.  A matrix is scaled so that its largest entry lies in [2^14, 2^15).
-// The activation scales come from bounds that hold for every input, so nothing can overflow FP16;
-// how far a bound lies above the values met decides what is left of lo's bits.  lo's unit is 2^-24,
-// so a value at 2^-k of a bound of 2^14 is kept to 2^(k - 39) of itself: to FP32's 2^-24 while
-// k <= 15.  The limits are 2^12 on activations and 2^10 on growth (weights of order one give 2^3
-// to 2^6); past them, or for a layer without weights, the model runs on the FP32 instructions.
-size_t split_plan(tn_model *m, const std::vector<double> &w, std::vector<SplitMat> &mats) {
+// Plans the split weights of a model the FP32 pair kernels cover; returns the element count of their
+// buffer (0: not covered).
+size_t split_plan(tn_model *m, std::vector<SplitMat> &mats) {
   SplitPlan &sp = m->split;
   sp = SplitPlan();
   if (!pair_kernels_support(m->F, m->K, m->L, false)) return 0;
   const int64_t F = m->F, K = m->K;
   const WeightOff &o = m->off;
-  struct Sums {
-    double top = 0.0, grow = 0.0;   // largest entry, largest column sum of |W|
-    std::vector<double> row;        // row sums of |W|
-  };
-  std::vector<double> col;
-  auto sums = [&](size_t at, int64_t n, int64_t kin) {
-    Sums r;
-    r.row.resize(n);
-    col.assign(kin, 0.0);
-    for (int64_t c = 0; c < n; ++c) {
-      const double *p = w.data() + at + c * kin;
-      double s = 0.0;
-      for (int64_t k = 0; k < kin; ++k) {
-        const double v = std::fabs(p[k]);
-        s += v;
-        col[k] += v;
-        r.top = v > r.top ? v : r.top;
-      }
-      r.row[c] = s;
-    }
-    for (double v : col) r.grow = std::max(r.grow, v);
-    return r;
-  };
-  bool ok = true;
   size_t total = 0;
-  auto pow2 = [&](int e) {
-    if (e < -100 || e > 100) ok = false;
-    return ok ? std::ldexp(1.0f, e) : 0.0f;
+  auto place = [&](size_t src, int64_t ncol, int64_t kin) {
+    const size_t at = total;
+    mats.push_back(SplitMat{(int64_t)src, (int64_t)at, (int32_t)ncol, (int32_t)kin});
+    total += (size_t)((ncol + 15) / 16 * ((kin + 31) / 32) * 1536);
+    return at;
   };
-  auto scale = [&](double top) { return top > 0.0 ? 14 - std::ilogb(top) : 0; };
-  auto place = [&](size_t src, int64_t ncol, int64_t kin, int e) {
-    SplitMat t;
-    t.src = (int64_t)src;
-    t.dst = (int64_t)total;
-    t.ncol = (int32_t)ncol;
-    t.kin = (int32_t)kin;
-    t.scale = pow2(e);
-    mats.push_back(t);
-    total += (size_t)((ncol + 15) / 16 * ((kin + 31) / 32) * 1024);
-    return (size_t)t.dst;
-  };
-  // the largest |W x + b| with inputs bounded by x (and silu >= -0.2785)
-  auto bound = [&](const Sums &r, size_t b, double x) {
-    double top = 0.28;
-    for (size_t c = 0; c < r.row.size(); ++c) top = std::max(top, std::fabs(w[b + c]) + x * r.row[c]);
-    return top;
-  };
-  const double kAct = 4096.0, kGrow = 1024.0, kTiny = 1e-6, kSiluGrad = 1.1;
-  const int ee = std::ilogb(kSplitE);
-  const int w0 = scale(sums(o.W0, 3 * F, K).top);
-  sp.W0 = place(o.W0f, 3 * F, K, w0);
-  sp.W0T = place(o.W0T, K, 3 * F, w0);
-  sp.i0 = pow2(-(ee + w0));
-  sp.j0 = pow2(-w0);
   auto mixing = [&](const size_t (&at)[3], const size_t (&atT)[3], SplitMix &x, SplitMix &xT) {
     for (int q = 0; q < 3; ++q) {
-      double top = 0.0;
-      for (int64_t k = 0; k < F * F; ++k) top = std::max(top, std::fabs(w[at[q] + k]));
-      const int e = scale(top);
-      x.at[q] = place(at[q], F, F, e);
-      xT.at[q] = place(atT[q], F, F, e);
-      x.s[q] = xT.s[q] = pow2(-e);
+      x.at[q] = place(at[q], F, F);
+      xT.at[q] = place(atT[q], F, F);
     }
   };
+  sp.W0 = place(o.W0f, 3 * F, K);
+  sp.W0T = place(o.W0T, K, 3 * F);
   mixing(o.Wmixf, o.WmixT, sp.mix, sp.mixT);
   sp.layer.resize(m->L);
   for (int l = 0; l < m->L; ++l) {
     const LayerOff &lo = o.layer[l];
     SplitLayer &s = sp.layer[l];
-    const Sums a = sums(lo.Wa, F, K), b = sums(lo.Wb, 2 * F, F), c = sums(lo.Wc, 3 * F, 2 * F);
-    const double B1 = bound(a, lo.ba, 1.0), B2 = bound(b, lo.bb, B1);
-    const double G2 = c.grow * kSiluGrad, G1 = b.grow * kSiluGrad;
-    if (!(B1 <= kAct && B2 <= kAct && G2 <= kGrow && G1 <= kGrow && G2 >= kTiny && G1 >= kTiny)) ok = false;
-    if (!ok) break;
     mixing(lo.W1f, lo.W1T, s.W1, s.W1T);
     mixing(lo.W2f, lo.W2T, s.W2, s.W2T);
-    const int wa = scale(a.top), wb = scale(b.top), wc = scale(c.top);
-    const int e1 = split_exp(B1), e2 = split_exp(B2);
-    const int g2 = (int)std::ceil(std::log2(G2 * 1.001)), g1 = (int)std::ceil(std::log2(G1 * 1.001));
-    s.Wa = place(lo.Waf, F, K, wa);
-    s.Wb = place(lo.Wbf, 2 * F, F, wb);
-    s.Wc = place(lo.Wcf, 3 * F, 2 * F, wc);
-    s.WaT = place(lo.WaT, K, F, wa);
-    s.WbT = place(lo.WbT, F, 2 * F, wb);
-    s.WcT = place(lo.WcT, 2 * F, 3 * F, wc);
-    s.s1 = pow2(e1);
-    s.s2 = pow2(e2);
-    s.i1 = pow2(-(ee + wa));
-    s.i2 = pow2(-(e1 + wb));
-    s.i3 = pow2(-(e2 + wc));
-    s.f2 = pow2(-(g2 + wc));
-    s.f1 = pow2(-(g1 + wb));
-    s.ja = pow2(g2 + g1 - wa);
+    s.Wa = place(lo.Waf, F, K);
+    s.Wb = place(lo.Wbf, 2 * F, F);
+    s.Wc = place(lo.Wcf, 3 * F, 2 * F);
+    s.WaT = place(lo.WaT, K, F);
+    s.WbT = place(lo.WbT, F, 2 * F);
+    s.WcT = place(lo.WcT, 2 * F, 3 * F);
   }
-  sp.ok = ok;
-  return ok ? total : 0;
+  return total;
 }
 
 // Uploads the packed weights and forms their copies on the device.
@@ -328,10 +260,10 @@ int upload_weights(tn_model *m, const std::vector<double> &packed) {
                      m->w32, m->w16);
   TN_LAUNCH_CHECK();
   std::vector<SplitMat> mats;
-  const size_t ns = split_plan(m, packed, mats);
+  const size_t ns = split_plan(m, mats);
   SplitMat *dev = nullptr;
   if (ns > 0) {
-    TN_HIP(hipMalloc(&m->wsplit, ns * sizeof(_Float16)));
+    TN_HIP(hipMalloc(&m->wsplit, ns * sizeof(__bf16)));
     TN_HIP(hipMalloc(&dev, mats.size() * sizeof(SplitMat)));
     int64_t most = 0;
     for (const SplitMat &t : mats) most = std::max<int64_t>(most, (t.ncol + 15) / 16 * (int64_t)((t.kin + 31) / 32));
@@ -394,40 +326,24 @@ std::vector<EventPair> g_events;
 
 namespace tn {
 
-bool split_args(const tn_model *m, PairFwdArgs &f) {
+void split_args(const tn_model *m, PairFwdArgs &f) {
   const SplitPlan &sp = m->split;
-  if (!sp.ok) return false;
-  f.sW0 = m->wsplit + sp.W0;
-  f.i0 = sp.i0;
+  f.W0 = m->wsplit + sp.W0;
   for (int l = 0; l < m->L; ++l) {
-    const SplitLayer &s = sp.layer[l];
-    f.sWa[l] = m->wsplit + s.Wa;
-    f.sWb[l] = m->wsplit + s.Wb;
-    f.sWc[l] = m->wsplit + s.Wc;
-    f.i1[l] = s.i1;
-    f.s1[l] = s.s1;
-    f.i2[l] = s.i2;
-    f.s2[l] = s.s2;
-    f.i3[l] = s.i3;
+    f.Wa[l] = m->wsplit + sp.layer[l].Wa;
+    f.Wb[l] = m->wsplit + sp.layer[l].Wb;
+    f.Wc[l] = m->wsplit + sp.layer[l].Wc;
   }
-  return true;
 }
 
-bool split_args(const tn_model *m, PairBwdArgs &b) {
+void split_args(const tn_model *m, PairBwdArgs &b) {
   const SplitPlan &sp = m->split;
-  if (!sp.ok) return false;
-  b.sW0T = m->wsplit + sp.W0T;
-  b.j0 = sp.j0;
+  b.W0T = m->wsplit + sp.W0T;
   for (int l = 0; l < m->L; ++l) {
-    const SplitLayer &s = sp.layer[l];
-    b.sWaT[l] = m->wsplit + s.WaT;
-    b.sWbT[l] = m->wsplit + s.WbT;
-    b.sWcT[l] = m->wsplit + s.WcT;
-    b.f2[l] = s.f2;
-    b.f1[l] = s.f1;
-    b.ja[l] = s.ja;
+    b.WaT[l] = m->wsplit + sp.layer[l].WaT;
+    b.WbT[l] = m->wsplit + sp.layer[l].WbT;
+    b.WcT[l] = m->wsplit + sp.layer[l].WcT;
   }
-  return true;
 }
 
 TimedScope::TimedScope(const char *name, hipStream_t s) {

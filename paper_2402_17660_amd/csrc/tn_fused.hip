@@ -137,7 +137,6 @@ template <bool BF16>
 int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, size_t ws_bytes) {
   using TA = typename std::conditional<BF16, float, double>::type;   // the islands' type
   using TH = typename std::conditional<BF16, __bf16, float>::type;   // the edge filters' type
-  using TY = TH;   // the type of the atom rows the gathers read (Y, dM)
   const int64_t N = pb.n, MP = pb.max_pairs, F = m->F, K = m->K, L = m->L;
   WsPlan plan(ws);
   FusedWs<TA> w;
@@ -162,21 +161,15 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
 
   // ---- all per-pair work of the forward pass in one MFMA kernel
   auto WB = [&](size_t off) { return static_cast<const __bf16 *>(m->w16 + off); };
-  const bool tiled = !BF16 && m->split.ok;
-  // Per-part channel mixing with one set of matrices (Wf: aligned copies, WT: their transposes):
-  // FP32 matrix-core kernel, or BF16 operands with FP32 accumulation in the BF16 path.
+  // BF16 path: per-part channel mixing with one set of matrices (Wf: aligned copies, WT: their
+  // transposes), BF16 operands with FP32 accumulation.  (FP32: launch_node_fwd, launch_node_bwd.)
   auto mixing = [&](const float *in, float *out, const size_t Wf[3], const size_t WT[3], int adjoint,
                     int accumulate, __bf16 *out16) -> int {
-    if (BF16) {
-      const size_t *off = adjoint ? WT : Wf;
-      const __bf16 *Bt[3] = {WB(off[0]), WB(off[1]), WB(off[2])};
-      return mix_bf16(s, in, out, N, F, Bt, accumulate, out16);
-    }
-    const float *Wm[3] = {W(Wf[0]), W(Wf[1]), W(Wf[2])};
-    const float *WmT[3] = {W(WT[0]), W(WT[1]), W(WT[2])};
-    return mix<float>(s, in, out, N, F, Wm, WmT, adjoint, accumulate, out16);
+    const size_t *off = adjoint ? WT : Wf;
+    const __bf16 *Bt[3] = {WB(off[0]), WB(off[1]), WB(off[2])};
+    return mix_bf16(s, in, out, N, F, Bt, accumulate, out16);
   };
-  // the same mixing of an input already rounded to BF16 (BF16 path only)
+  // the same mixing of an input already rounded to BF16
   auto mixing16 = [&](const __bf16 *in, float *out, const size_t Wf[3], const size_t WT[3], int adjoint,
                       int accumulate) -> int {
     const size_t *off = adjoint ? WT : Wf;
@@ -221,21 +214,16 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
   } else {
     PairFwdArgs pf;
     fill_common(pf);
-    pf.W0 = W(o.W0f);
     pf.b0 = W(o.b0);
     pf.b0lo = W(o.b0lo);
     for (int64_t l = 0; l < L; ++l) {
       const LayerOff &lo = o.layer[l];
-      pf.Wa[l] = W(lo.Waf);
       pf.ba[l] = W(lo.ba);
-      pf.Wb[l] = W(lo.Wbf);
       pf.bb[l] = W(lo.bb);
-      pf.Wc[l] = W(lo.Wcf);
       pf.bc[l] = W(lo.bc);
       pf.z1[l] = w.z1[l];
       pf.z2[l] = w.z2[l];
       pf.z3[l] = w.z3[l];
-      pf.h[l] = nullptr;   // not stored: the message gathers form it from z3 and phi
     }
     pf.geo = w.geo;
     pf.phi = w.phi;
@@ -250,7 +238,7 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
                            reinterpret_cast<const TH *>(w.f0), w.Xr)))
     return rc;
   if constexpr (!BF16) {
-    if (tiled && N > 0) {
+    if (N > 0) {
       if (F == 64)
         hipLaunchKernelGGL(k_norm_layernorm<64>, dim3(layernorm_grid(N)), dim3(256), 0, s, N, w.Xr, WA(o.ln_g),
                            WA(o.ln_b), w.n0, w.xhat0, w.rstd0);
@@ -259,8 +247,7 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
                            WA(o.ln_b), w.n0, w.xhat0, w.rstd0);
       TN_LAUNCH_CHECK();
     }
-  }
-  if (!tiled && N > 0) {
+  } else if (N > 0) {
     hipLaunchKernelGGL((k_node_norm<TA, float>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.Xr, w.nrm0);
     TN_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_layernorm<TA>, dim3(layernorm_grid(N)), dim3(256), 0, s, N, (int)F, w.nrm0, WA(o.ln_g),
@@ -269,43 +256,38 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
   }
   if ((rc = linear_fwd<TA>(s, w.n0, N, F, WA(o.W1), WA(o.b1), 2 * F, w.ea1, w.ez1, 1))) return rc;
   if ((rc = linear_fwd<TA>(s, w.ea1, N, 2 * F, WA(o.W2), WA(o.b2), 3 * F, w.g, w.ez2, 1))) return rc;
-  // node steps between the gathers as one launch each, on split operands
-  if constexpr (!BF16) {
-    if (tiled) {
-      NodeFwdArgs nf;
-      nf.N = N;
-      nf.in = w.Xr;
-      nf.g = w.g;
-      nf.mid = w.T0;
-      nf.Xo = w.X[0];
-      nf.ln_g = WA(o.oln_g);
-      nf.ln_b = WA(o.oln_b);
-      nf.q = w.q;
-      nf.xhat = w.oxhat;
-      nf.rstd = w.orstd;
-      nf.A = split_mix(m, m->split.mix);
-      for (int64_t l = 0; l <= L; ++l) {   // the step before layer l, or before the output network
-        const bool last = l == L;
-        if (!last) {
-          nf.Y = w.Y[l];
-          nf.B = split_mix(m, m->split.layer[l].W1);
-        }
-        if ((rc = launch_node_fwd(s, (int)F, l == 0, last, nf))) return rc;
-        if (last) break;
-        if ((rc = message_product_w(s, F, N, rowptr, nbr, pid, np, MP, (const float *)w.z3[l], (const float *)w.phi,
-                                    (const float *)w.Y[l], w.Pb[l], w.Y[l], w.M[l], w.P[l], w.nP[l])))
-          return rc;
-        nf.in = w.Pb[l];
-        nf.X = w.X[l];
-        nf.mid = w.D[l];
-        nf.Xo = w.X[l + 1];
-        nf.A = split_mix(m, m->split.layer[l].W2);
+  if constexpr (!BF16) {   // node steps between the gathers as one launch each, on split operands
+    NodeFwdArgs nf;
+    nf.N = N;
+    nf.in = w.Xr;
+    nf.g = w.g;
+    nf.mid = w.T0;
+    nf.Xo = w.X[0];
+    nf.ln_g = WA(o.oln_g);
+    nf.ln_b = WA(o.oln_b);
+    nf.q = w.q;
+    nf.xhat = w.oxhat;
+    nf.rstd = w.orstd;
+    nf.A = split_mix(m, m->split.mix);
+    for (int64_t l = 0; l <= L; ++l) {   // the step before layer l, or before the output network
+      const bool last = l == L;
+      if (!last) {
+        nf.Y = w.Y[l];
+        nf.B = split_mix(m, m->split.layer[l].W1);
       }
+      if ((rc = launch_node_fwd(s, (int)F, l == 0, last, nf))) return rc;
+      if (last) break;
+      if ((rc = message_product_w(s, F, N, rowptr, nbr, pid, np, MP, (const float *)w.z3[l], (const float *)w.phi,
+                                  (const float *)w.Y[l], w.Pb[l], w.Y[l], w.M[l], w.P[l], w.nP[l])))
+        return rc;
+      nf.in = w.Pb[l];
+      nf.X = w.X[l];
+      nf.mid = w.D[l];
+      nf.Xo = w.X[l + 1];
+      nf.A = split_mix(m, m->split.layer[l].W2);
     }
-  }
-  if (!tiled) {
-    // the embedding's channel mixing is linear in the FP32 features and runs in FP32 (BF16 operands
-    // in the BF16 path); the gating product is formed in FP64 and rounded once
+  } else {
+    // the gating product is formed in the islands' type and rounded once
     if ((rc = mixing(w.Xr, w.T0, o.Wmixf, o.WmixT, 0, 0, nullptr))) return rc;
     // (with layers, the gating also normalises the first layer's input)
     if (N > 0 && L > 0) {
@@ -320,24 +302,13 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
     // ---- interaction layers: mix, message+product, mix, residual(+normalise)
     for (int64_t l = 0; l < L; ++l) {
       const LayerOff &lo = o.layer[l];
-      __bf16 *y16 = BF16 ? w.Y16[l] : nullptr;
-      if ((rc = mixing(w.Xb[l], w.Y[l], lo.W1f, lo.W1T, 0, 0, y16))) return rc;
-      // the neighbours' rows from the BF16 copy in the BF16 path
-      const TY *yg = BF16 ? reinterpret_cast<const TY *>(y16) : reinterpret_cast<const TY *>(w.Y[l]);
-      // z3, from which the gathers form h = phi silu(z3)
-      const TH *hl = reinterpret_cast<const TH *>(w.z3[l]);
-      const float *hphi = w.phi;
-      if (BF16) {
-        if ((rc = message_product_w(s, F, N, rowptr, nbr, pid, np, MP, hl, hphi, yg, w.mix16, w.Y[l], w.M[l],
-                                    w.P[l], w.nP[l])))
-          return rc;
-        if ((rc = mixing16(w.mix16, w.D[l], lo.W2f, lo.W2T, 0, 0))) return rc;
-      } else {
-        if ((rc = message_product_w(s, F, N, rowptr, nbr, pid, np, MP, hl, hphi, yg, w.Pb[l], w.Y[l], w.M[l],
-                                    w.P[l], w.nP[l])))
-          return rc;
-        if ((rc = mixing(w.Pb[l], w.D[l], lo.W2f, lo.W2T, 0, 0, nullptr))) return rc;
-      }
+      if ((rc = mixing(w.Xb[l], w.Y[l], lo.W1f, lo.W1T, 0, 0, w.Y16[l]))) return rc;
+      // the neighbours' rows from the BF16 copy; z3, from which the gathers form h = phi silu(z3)
+      if ((rc = message_product_w(s, F, N, rowptr, nbr, pid, np, MP, reinterpret_cast<const __bf16 *>(w.z3[l]),
+                                  (const float *)w.phi, (const __bf16 *)w.Y16[l], w.mix16, w.Y[l], w.M[l], w.P[l],
+                                  w.nP[l])))
+        return rc;
+      if ((rc = mixing16(w.mix16, w.D[l], lo.W2f, lo.W2T, 0, 0))) return rc;
       if (N > 0) {
         if (l + 1 < L) {
           hipLaunchKernelGGL(k_residual_normalize<float>, dim3(gNF), dim3(bs), 0, s, N, (int)F, w.Xb[l], w.D[l],
@@ -351,7 +322,7 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
   }
   // ---- output network (FP64) and energies
   const int64_t H = F / 2;
-  if (!tiled && N > 0) {
+  if (BF16 && N > 0) {
     hipLaunchKernelGGL((k_out_norms<TA, float>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.X[L], w.on);
     TN_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_layernorm<TA>, dim3(layernorm_grid(N)), dim3(256), 0, s, N, (int)(3 * F), w.on, WA(o.oln_g),
@@ -381,7 +352,7 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
   // ================================================================ reverse sweep
   if ((rc = linear_bwd<TA>(s, w.dhz, N, H, WA(o.Wh), F, w.dox, w.oz, 0))) return rc;
   if ((rc = linear_bwd<TA>(s, w.dox, N, F, WA(o.Wo), 3 * F, w.dq, nullptr, 0))) return rc;
-  if (!tiled && N > 0) {
+  if (BF16 && N > 0) {
     hipLaunchKernelGGL(k_layernorm_bwd<TA>, dim3(layernorm_grid(N)), dim3(256), 0, s, N, (int)(3 * F), w.dq, w.oxhat,
                        w.orstd, WA(o.oln_g), w.don);
     TN_LAUNCH_CHECK();
@@ -389,100 +360,73 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
     TN_LAUNCH_CHECK();
   }
   if constexpr (!BF16) {
-    if (tiled) {
-      NodeBwdArgs nb;
-      nb.N = N;
-      nb.dq = w.dq;
-      nb.xhat = w.oxhat;
-      nb.rstd = w.orstd;
-      nb.ln_g = WA(o.oln_g);
-      nb.dX = w.dX;
-      nb.dY = w.dY;
-      nb.T0 = w.T0;
-      nb.g = w.g;
-      nb.ez = w.ez2;
-      nb.dez = w.dez2;
-      nb.dXr = w.dXr;
-      for (int64_t l = L; l >= 0; --l) {   // the step after layer l's adjoint messages, down to layer l - 1's
-        nb.X = w.X[l];
-        if (l > 0) {
-          nb.D = w.D[l - 1];
-          nb.Y = w.Y[l - 1];
-          nb.M = w.M[l - 1];
-          nb.dM = w.dM[l - 1];
-          nb.B = split_mix(m, m->split.layer[l - 1].W2T);
-        } else {
-          nb.B = split_mix(m, m->split.mixT);
-        }
-        if ((rc = launch_node_bwd(s, (int)F, l == L, l == 0, nb))) return rc;
-        if (l == 0) break;
-        if ((rc = message_w(s, F, N, rowptr, nbr, pid, np, MP, (const float *)w.z3[l - 1], (const float *)w.phi,
-                            (const float *)w.dM[l - 1], w.dY, 1, (const float *)nullptr)))
-          return rc;
-        nb.A = split_mix(m, m->split.layer[l - 1].W1T);
+    NodeBwdArgs nb;
+    nb.N = N;
+    nb.dq = w.dq;
+    nb.xhat = w.oxhat;
+    nb.rstd = w.orstd;
+    nb.ln_g = WA(o.oln_g);
+    nb.dX = w.dX;
+    nb.dY = w.dY;
+    nb.T0 = w.T0;
+    nb.g = w.g;
+    nb.ez = w.ez2;
+    nb.dez = w.dez2;
+    nb.dXr = w.dXr;
+    for (int64_t l = L; l >= 0; --l) {   // the step after layer l's adjoint messages, down to layer l - 1's
+      nb.X = w.X[l];
+      if (l > 0) {
+        nb.D = w.D[l - 1];
+        nb.Y = w.Y[l - 1];
+        nb.M = w.M[l - 1];
+        nb.dM = w.dM[l - 1];
+        nb.B = split_mix(m, m->split.layer[l - 1].W2T);
+      } else {
+        nb.B = split_mix(m, m->split.mixT);
       }
+      if ((rc = launch_node_bwd(s, (int)F, l == L, l == 0, nb))) return rc;
+      if (l == 0) break;
+      if ((rc = message_w(s, F, N, rowptr, nbr, pid, np, MP, (const float *)w.z3[l - 1], (const float *)w.phi,
+                          (const float *)w.dM[l - 1], w.dY, 1, (const float *)nullptr)))
+        return rc;
+      nb.A = split_mix(m, m->split.layer[l - 1].W1T);
     }
-  }
-  if (!tiled) {
+  } else {
     for (int64_t l = L - 1; l >= 0; --l) {
       const LayerOff &lo = o.layer[l];
-      if (BF16) {
-        if (N > 0) {
-          hipLaunchKernelGGL((k_residual_bwd<float, __bf16>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.D[l], w.dX,
-                             w.mix16);
-          TN_LAUNCH_CHECK();
-        }
-        if ((rc = mixing16(w.mix16, w.dPb, lo.W2f, lo.W2T, 1, 0))) return rc;
-      } else {
-        if (N > 0) {
-          hipLaunchKernelGGL(k_residual_bwd<float>, dim3(gNF), dim3(bs), 0, s, N, (int)F, w.D[l], w.dX, w.dD);
-          TN_LAUNCH_CHECK();
-        }
-        if ((rc = mixing(w.dD, w.dPb, lo.W2f, lo.W2T, 1, 0, nullptr))) return rc;
-      }
       if (N > 0) {
-        hipLaunchKernelGGL(k_product_bwd<float>, dim3(gNF), dim3(bs), 0, s, N, (int)F, w.dPb, w.P[l], w.nP[l], w.Y[l],
-                           w.M[l], w.dY, w.dM[l], BF16 ? w.dM16[l] : nullptr);
+        hipLaunchKernelGGL((k_residual_bwd<float, __bf16>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.D[l], w.dX,
+                           w.mix16);
         TN_LAUNCH_CHECK();
       }
-      const TY *dmg = BF16 ? reinterpret_cast<const TY *>(w.dM16[l]) : reinterpret_cast<const TY *>(w.dM[l]);
-      const TH *hl = reinterpret_cast<const TH *>(w.z3[l]);
-      const float *hphi = w.phi;
-      if (BF16) {   // dY + the gathered sum, rounded to BF16 for the mixing
-        if ((rc = message_w(s, F, N, rowptr, nbr, pid, np, MP, hl, hphi, dmg, w.mix16, 1, (const float *)w.dY)))
-          return rc;
-        if ((rc = mixing16(w.mix16, w.dX, lo.W1f, lo.W1T, 1, 1))) return rc;
-      } else {
-        if ((rc = message_w(s, F, N, rowptr, nbr, pid, np, MP, hl, hphi, dmg, w.dY, 1, (const float *)nullptr)))
-          return rc;
-        if ((rc = mixing(w.dY, w.dX, lo.W1f, lo.W1T, 1, 1, nullptr))) return rc;
+      if ((rc = mixing16(w.mix16, w.dPb, lo.W2f, lo.W2T, 1, 0))) return rc;
+      if (N > 0) {
+        hipLaunchKernelGGL(k_product_bwd<float>, dim3(gNF), dim3(bs), 0, s, N, (int)F, w.dPb, w.P[l], w.nP[l], w.Y[l],
+                           w.M[l], w.dY, w.dM[l], w.dM16[l]);
+        TN_LAUNCH_CHECK();
       }
+      // dY + the gathered sum, rounded to BF16 for the mixing
+      if ((rc = message_w(s, F, N, rowptr, nbr, pid, np, MP, reinterpret_cast<const __bf16 *>(w.z3[l]),
+                          (const float *)w.phi, (const __bf16 *)w.dM16[l], w.mix16, 1, (const float *)w.dY)))
+        return rc;
+      if ((rc = mixing16(w.mix16, w.dX, lo.W1f, lo.W1T, 1, 1))) return rc;
       if (N > 0) {
         hipLaunchKernelGGL(k_normalize_bwd<float>, dim3(gNF), dim3(bs), 0, s, N, (int)F, w.X[l], w.nX[l], w.dX);
         TN_LAUNCH_CHECK();
       }
     }
-    // ---- embedding adjoint, node part in FP64
-    if (BF16) {
-      if (N > 0) {
-        hipLaunchKernelGGL((k_gate_bwd<TA, float, __bf16>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.dX, w.T0, w.g,
-                           w.dez2, w.mix16, w.ez2);
-        TN_LAUNCH_CHECK();
-      }
-      if ((rc = mixing16(w.mix16, w.dXr, o.Wmixf, o.WmixT, 1, 0))) return rc;
-    } else {
-      if (N > 0) {
-        hipLaunchKernelGGL((k_gate_bwd<TA, float>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.dX, w.T0, w.g, w.dez2,
-                           w.dT0, w.ez2);
-        TN_LAUNCH_CHECK();
-      }
-      if ((rc = mixing(w.dT0, w.dXr, o.Wmixf, o.WmixT, 1, 0, nullptr))) return rc;
+    // ---- embedding adjoint, node part
+    if (N > 0) {
+      hipLaunchKernelGGL((k_gate_bwd<TA, float, __bf16>), dim3(gNF), dim3(bs), 0, s, N, (int)F, w.dX, w.T0, w.g,
+                         w.dez2, w.mix16, w.ez2);
+      TN_LAUNCH_CHECK();
     }
+    if ((rc = mixing16(w.mix16, w.dXr, o.Wmixf, o.WmixT, 1, 0))) return rc;
   }
   if ((rc = linear_bwd<TA>(s, w.dez2, N, 3 * F, WA(o.W2), 2 * F, w.dez1, w.ez1, 0))) return rc;
   if ((rc = linear_bwd<TA>(s, w.dez1, N, 2 * F, WA(o.W1), F, w.dn0, nullptr, 0))) return rc;
   if constexpr (!BF16) {
-    if (tiled && N > 0) {
+    if (N > 0) {
       if (F == 64)
         hipLaunchKernelGGL(k_norm_layernorm_bwd<64>, dim3(layernorm_grid(N)), dim3(256), 0, s, N, w.dn0, w.xhat0,
                            w.rstd0, WA(o.ln_g), w.Xr, w.dXr);
@@ -491,8 +435,7 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
                            w.rstd0, WA(o.ln_g), w.Xr, w.dXr);
       TN_LAUNCH_CHECK();
     }
-  }
-  if (!tiled && N > 0) {
+  } else if (N > 0) {
     hipLaunchKernelGGL(k_layernorm_bwd<TA>, dim3(layernorm_grid(N)), dim3(256), 0, s, N, (int)F, w.dn0, w.xhat0, w.rstd0,
                        WA(o.ln_g), w.dnrm0);
     TN_LAUNCH_CHECK();
@@ -528,7 +471,6 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
   } else {
     PairBwdArgs pbw;
     fill_common(pbw);
-    pbw.W0T = W(o.W0T);
     pbw.g.z = zz;
     pbw.g.U = W(o.U);
     pbw.g.V = W(o.V);
@@ -536,10 +478,6 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
     pbw.g.f0 = w.f0;
     pbw.g.dXr = w.dXr;
     for (int64_t l = 0; l < L; ++l) {
-      const LayerOff &lo = o.layer[l];
-      pbw.WaT[l] = W(lo.WaT);
-      pbw.WbT[l] = W(lo.WbT);
-      pbw.WcT[l] = W(lo.WcT);
       pbw.z1[l] = w.z1[l];
       pbw.z2[l] = w.z2[l];
       pbw.z3[l] = w.z3[l];

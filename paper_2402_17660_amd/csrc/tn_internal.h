@@ -52,34 +52,21 @@ struct WeightOff {
   size_t total;     // element count of one packed copy
 };
 
-// The pair kernels' weights as FP16 hi/lo halves (tn_mfma.h), packed by fragment, each matrix
-// scaled by a power of two, and the powers of two that scale the activations.  Element offsets
-// into tn_model::wsplit.
-//   forward  the basis e <= 1 is scaled by kSplitE; silu(z1) and silu(z2) by s1 and s2, from the
-//            bounds |z1| <= max_c (sum_k |Wa_ck| + |ba_c|) and so on, which hold for every input;
-//            i0 .. i3 take a product's scales off again
-//   reverse  each pair's adjoint row is scaled by its own largest entry (row factors in LDS); f2
-//            and f1 take the weight's scale off and the growth bound max_c sum_n |W_nc| of dz2 and
-//            dz1 down, j0 and ja take all but the row factor off dE/de
-// The channel mixings' matrices too (I, A, S; as they are, T: transposed), with the factor that
-// takes each one's scale off; their operands are scaled as they are staged (tn_nodetile.h).
+// The FP32 path's weights as the three BF16 parts of each number (tn_mfma.h), taken from the FP64
+// weights and packed by fragment: element offsets into tn_model::wsplit of the pair kernels' matrices
+// and the channel mixings' (I, A, S; as they are, T: transposed).
 struct SplitMix {
   size_t at[3] = {0, 0, 0};
-  float s[3] = {0, 0, 0};
 };
 struct SplitLayer {
   SplitMix W1, W1T, W2, W2T;
   size_t Wa = 0, Wb = 0, Wc = 0, WaT = 0, WbT = 0, WcT = 0;
-  float i1 = 0, s1 = 0, i2 = 0, s2 = 0, i3 = 0, f2 = 0, f1 = 0, ja = 0;
 };
 struct SplitPlan {
-  bool ok = false;   // the bounds leave every operand its 24 bits (split_plan)
   size_t W0 = 0, W0T = 0;
-  float i0 = 0, j0 = 0;
   SplitMix mix, mixT;   // the embedding's
   std::vector<SplitLayer> layer;
 };
-constexpr float kSplitE = 16384.0f;
 
 }  // namespace tn
 
@@ -97,7 +84,7 @@ struct tn_model {
   float *w32 = nullptr;            // packed FP32 weights (device)
   __bf16 *w16 = nullptr;           // packed BF16 weights (device)
   tn::SplitPlan split;
-  _Float16 *wsplit = nullptr;      // the pair kernels' weights as FP16 hi/lo halves (device)
+  __bf16 *wsplit = nullptr;        // the FP32 path's weights in BF16 parts (device; null: sizes it does not take)
   void *mol_const = nullptr;       // the molecule path's weight pointers (device; tn_mol.hip)
 };
 
@@ -225,17 +212,14 @@ struct PairFwdArgs {
   Lattice lat;   // periodic cell (lat.periodic == 0: isolated systems)
   double r_c = 0, r_lo = 0, alpha = 0;
   const double *mu = nullptr, *beta = nullptr;
-  const float *W0 = nullptr, *b0 = nullptr, *b0lo = nullptr;   // b0lo: what b0's rounding leaves out
-  const float *Wa[kMaxLayers], *ba[kMaxLayers], *Wb[kMaxLayers], *bb[kMaxLayers], *Wc[kMaxLayers], *bc[kMaxLayers];
+  const __bf16 *W0 = nullptr, *Wa[kMaxLayers], *Wb[kMaxLayers], *Wc[kMaxLayers];   // split weights (SplitPlan)
+  const float *b0 = nullptr, *b0lo = nullptr;   // b0lo: what b0's rounding leaves out
+  const float *ba[kMaxLayers], *bb[kMaxLayers], *bc[kMaxLayers];
   int L = 0;
   float *geo = nullptr, *phi = nullptr, *f0 = nullptr;
   // per pair and layer: z1, z2 hold silu'(z1), silu'(z2) (the reverse pass's only use of them),
-  // z3 the pre-activation itself, h the filters phi silu(z3) (null: not stored, and never stored by
-  // the split kernels; the fused and molecule paths form them from z3 in the message gathers)
-  float *z1[kMaxLayers], *z2[kMaxLayers], *z3[kMaxLayers], *h[kMaxLayers];
-  // split weights and scales (SplitPlan), for the split kernels; W0, Wa, Wb, Wc for the FP32 ones
-  const _Float16 *sW0 = nullptr, *sWa[kMaxLayers], *sWb[kMaxLayers], *sWc[kMaxLayers];
-  float i0 = 0, i1[kMaxLayers], s1[kMaxLayers], i2[kMaxLayers], s2[kMaxLayers], i3[kMaxLayers];
+  // z3 the pre-activation itself (the message gathers form the filters phi silu(z3) from it)
+  float *z1[kMaxLayers], *z2[kMaxLayers], *z3[kMaxLayers];
 };
 
 // Per-atom rows the reverse pair kernels gather (internal atom order, [N][9][F] coordinates).
@@ -257,20 +241,16 @@ struct PairBwdArgs {
   Lattice lat;   // periodic cell (lat.periodic == 0: isolated systems)
   double r_c = 0, r_lo = 0, alpha = 0;
   const double *mu = nullptr, *beta = nullptr;
-  const float *W0T = nullptr;
-  const float *WaT[kMaxLayers], *WbT[kMaxLayers], *WcT[kMaxLayers];
+  const __bf16 *W0T = nullptr, *WaT[kMaxLayers], *WbT[kMaxLayers], *WcT[kMaxLayers];   // split weights
   int L = 0;
   const float *z1[kMaxLayers], *z2[kMaxLayers], *z3[kMaxLayers];
   BwdGather g;
   float *gpair = nullptr;
-  const _Float16 *sW0T = nullptr, *sWaT[kMaxLayers], *sWbT[kMaxLayers], *sWcT[kMaxLayers];
-  float j0 = 0, f2[kMaxLayers], f1[kMaxLayers], ja[kMaxLayers];
 };
 
-// The model's split weights and scales into the pair kernels' arguments; false (nothing set) for
-// a model outside the split's range, whose pair kernels run on FP32 instructions.
-bool split_args(const tn_model *m, PairFwdArgs &f);
-bool split_args(const tn_model *m, PairBwdArgs &b);
+// The model's split weights into the pair kernels' arguments.
+void split_args(const tn_model *m, PairFwdArgs &f);
+void split_args(const tn_model *m, PairBwdArgs &b);
 
 int launch_pair_fwd(hipStream_t s, int F, int K, const PairFwdArgs &a, int variant);
 int launch_pair_bwd(hipStream_t s, int F, int K, const PairBwdArgs &a, int variant);

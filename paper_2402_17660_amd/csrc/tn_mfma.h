@@ -12,7 +12,9 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
 }
 
 // mfma4 with the activation fragment a and the weight fragment b; with TR the weights are the
-// instruction's first operand, so the accumulator holds the product transposed (see wave_mm_t).
+// instruction's first operand, so the accumulator holds the product transposed: entry t of
+// acc[rb][cb] in lane l is D_rb[l%16][col0 + cb*16 + 4(l/16) + t], four consecutive columns of one
+// row, which a row-major store or load moves in one vector access.
 template <bool TR>
 __device__ __forceinline__ floatx4 mfma4_ab(float a, float b, floatx4 c) {
   return TR ? mfma4(b, a, c) : mfma4(a, b, c);
@@ -42,83 +44,112 @@ __device__ __forceinline__ void st4(__bf16 *p, const floatx4 &v) {
   *reinterpret_cast<bf16x4 *>(p) = o;
 }
 
-// FP32 products on the FP16 matrix instructions.  A float x, scaled by a power of two into FP16's
-// range, is split into hi = fp16(x) and lo = fp16(x - hi): |x - hi| <= 2^-12 |x|, so hi + lo is x to
-// 2^-24, the rounding of FP32 itself (as long as lo is not far below FP16's smallest number,
-// 2^-24; the scales put the largest entry at 2^14 or above).  A product is then hi hi + hi lo +
-// lo hi with FP32 accumulation (lo lo, 2^-24 of it, is dropped): three v_mfma_f32_16x16x32_f16 do
-// the work of eight v_mfma_f32_16x16x4_f32 at a fifth of the cycles (16 against 32 each).
-// Measured against 64-bit sums over K = 128, 256 and 384 normal products: 1.4e-7, 1.9e-7 and
-// 2.2e-7 of the result's RMS, the FP32 instruction 2.0e-7, 2.8e-7 and 3.4e-7 (it rounds the
-// running sum every fourth product); at K = 32, 0.9e-7 against 1.0e-7.
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+// FP32 products on the BF16 matrix instructions.  An FP32 number x is the sum of three BF16 numbers of its
+// sign and exponent range: h = bf16(x), m = bf16(x - h) and l = x - h - m, all rounded to nearest.
+// Both differences are exact, and l has the bits that are left of the 24 (|m| <= 2^-8 |x|, |l| <=
+// 2^-17 |x|), so h + m + l is x itself, with no scale to choose and whatever other entries its
+// matrix or row has (for |x| >= 2^-110; below, l ends at BF16's smallest number, 2^-133).  A product
+// is the six largest of the nine BF16 products with FP32 accumulation; the three left out (m l, l m,
+// l l) are at most 2^-24 of it together, of either sign, and 2^-27.4 in RMS.  Six
+// v_mfma_f32_16x16x32_bf16 do the work of eight v_mfma_f32_16x16x4_f32 in 96 matrix cycles instead
+// of 256.  Two parts are not enough: of FP16's 11 bits each they hold 23, and a rounding of a weight is the
+// same in every pair and atom.
 constexpr int kPadH = 8;   // LDS row padding of split operand tiles (elements)
 
-__device__ __forceinline__ floatx4 mfma_f16(const half8 &a, const half8 &b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+// V values (1, 2 or 4) as their three parts, each as one store at p, p + plane and p + 2 plane.  The
+// remainders are those of the rounded x: a product that ends in x may not be fused into them.
+template <int V>
+__device__ __forceinline__ void st_split(__bf16 *p, int plane, const float (&x)[V]) {
+#pragma clang fp contract(off)
+  typedef __bf16 part __attribute__((ext_vector_type(V)));
+  float r[V];
+#pragma unroll
+  for (int t = 0; t < V; ++t) r[t] = x[t];
+#pragma unroll
+  for (int n = 0; n < 3; ++n) {
+    part o;
+#pragma unroll
+    for (int t = 0; t < V; ++t) {
+      o[t] = (__bf16)r[t];
+      r[t] -= (float)o[t];
+    }
+    *reinterpret_cast<part *>(p + n * plane) = o;
+  }
+}
+__device__ __forceinline__ void st4_split(__bf16 *p, int plane, const floatx4 &v) {
+  const float x[4] = {v[0], v[1], v[2], v[3]};
+  st_split<4>(p, plane, x);
 }
 
-// Four values, already scaled, as their hi and lo halves (8-byte stores at p and p + lo).
-__device__ __forceinline__ void st4_split(_Float16 *p, int lo, const floatx4 &v) {
-  half4 h, l;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    h[t] = (_Float16)v[t];
-    l[t] = (_Float16)(v[t] - (float)h[t]);
-  }
-  *reinterpret_cast<half4 *>(p) = h;
-  *reinterpret_cast<half4 *>(p + lo) = l;
+// One fragment's three parts.
+struct Frag3 {
+  bf16x8 h, m, l;
+};
+__device__ __forceinline__ Frag3 ld_frag3(const __bf16 *p, int plane) {
+  return Frag3{*reinterpret_cast<const bf16x8 *>(p), *reinterpret_cast<const bf16x8 *>(p + plane),
+               *reinterpret_cast<const bf16x8 *>(p + 2 * plane)};
 }
+
+// acc[n] += w[n] a for the N weight fragments w: the six products, smallest first, each over all n.
+template <int N>
+__device__ __forceinline__ void mfma_split(const Frag3 (&w)[N], const Frag3 &a, floatx4 (&acc)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].l, a.h, acc[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].h, a.l, acc[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].m, a.m, acc[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].m, a.h, acc[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].h, a.m, acc[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].h, a.h, acc[n]);
+}
+
+// This wave's weights of a product in KC chunks of 32 along K: column blocks cb0 .. cb0 + NB - 1, packed by
+// fragment (k_split_pack): block (column block, chunk) holds 64 lanes x 8 h, then m, then l, so a
+// wave's loads are 1 KB without gaps.  The first PD chunks are loaded at once: before the stores and barriers
+// that precede the product, whose end the wait for a later load would also wait for.
+constexpr int kSplitBlock = 3 * 512;
+template <int NB, int KC, int PD>
+struct SplitWeights {
+  const __bf16 *p;
+  Frag3 next[PD][NB];
+  __device__ __forceinline__ void load(int kc, Frag3 (&f)[NB]) const {
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) f[cb] = ld_frag3(p + ((size_t)cb * KC + kc) * kSplitBlock, 512);
+  }
+  __device__ __forceinline__ SplitWeights(const __bf16 *__restrict__ B, int cb0)
+      : p(B + (size_t)cb0 * KC * kSplitBlock + (threadIdx.x & 63) * 8) {
+#pragma unroll
+    for (int d = 0; d < PD; ++d)
+      if (d < KC) load(d, next[d]);
+  }
+};
 
 // acc[rb][cb] += act_rb * Bt^T from split operands: row i of the activations starts at act + i*ld
-// (LDS, hi halves; the lo halves `lo` elements further), KC chunks of 32 along K.  The weights are
-// packed by fragment (split_pack): block (column block, chunk) holds 64 lanes x 8 hi halves, then
-// the lo halves, so a wave's loads are 1 KB without gaps.  The weights are the instruction's first
+// (LDS, h; m and l `plane` and 2 `plane` elements further).  The weights are the instruction's first
 // operand: entry t of acc[rb][cb] in lane l is D[rb*16 + l%16][(cb0 + cb)*16 + 4(l/16) + t].
 // The weights of the next PD chunks are in flight while the current chunk's products run.
-template <int RB, int NB, int KC, int PD = 1>
-__device__ __forceinline__ void wave_mm_split(const _Float16 *act, int lo, int ld, const _Float16 *__restrict__ B,
-                                              int cb0, floatx4 (&acc)[RB][NB]) {
+template <int RB, int NB, int KC, int PD>
+__device__ __forceinline__ void wave_mm_split(const __bf16 *act, int plane, int ld, SplitWeights<NB, KC, PD> &B,
+                                              floatx4 (&acc)[RB][NB]) {
   const int lane = threadIdx.x & 63;
-  const _Float16 *ap = act + (lane & 15) * ld + 8 * (lane >> 4);
-  const _Float16 *bp = B + (size_t)cb0 * KC * 1024 + lane * 8;
-  half8 nh[PD][NB], nl[PD][NB];
-  auto load = [&](int kc, half8 (&h)[NB], half8 (&l)[NB]) {
+  const __bf16 *ap = act + (lane & 15) * ld + 8 * (lane >> 4);
+  auto chunk = [&](int kc, Frag3 (&f)[NB]) {
+    Frag3 w[NB];
 #pragma unroll
-    for (int cb = 0; cb < NB; ++cb) {
-      h[cb] = *reinterpret_cast<const half8 *>(bp + ((size_t)cb * KC + kc) * 1024);
-      l[cb] = *reinterpret_cast<const half8 *>(bp + ((size_t)cb * KC + kc) * 1024 + 512);
-    }
+    for (int cb = 0; cb < NB; ++cb) w[cb] = f[cb];
+    if (kc + PD < KC) B.load(kc + PD, f);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) mfma_split(w, ld_frag3(ap + rb * 16 * ld + 32 * kc, plane), acc[rb]);
   };
-  auto chunk = [&](int kc, half8 (&sh)[NB], half8 (&sl)[NB]) {
-    half8 bh[NB], bl[NB];
-#pragma unroll
-    for (int cb = 0; cb < NB; ++cb) {
-      bh[cb] = sh[cb];
-      bl[cb] = sl[cb];
-    }
-    if (kc + PD < KC) load(kc + PD, sh, sl);
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const half8 ah = *reinterpret_cast<const half8 *>(ap + rb * 16 * ld + 32 * kc);
-      const half8 al = *reinterpret_cast<const half8 *>(ap + rb * 16 * ld + 32 * kc + lo);
-#pragma unroll
-      for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = mfma_f16(bl[cb], ah, acc[rb][cb]);
-#pragma unroll
-      for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = mfma_f16(bh[cb], al, acc[rb][cb]);
-#pragma unroll
-      for (int cb = 0; cb < NB; ++cb) acc[rb][cb] = mfma_f16(bh[cb], ah, acc[rb][cb]);
-    }
-  };
-#pragma unroll
-  for (int d = 0; d < PD; ++d)
-    if (d < KC) load(d, nh[d], nl[d]);
   if constexpr (PD == 1) {
-    for (int kc = 0; kc < KC; ++kc) chunk(kc, nh[0], nl[0]);
+    for (int kc = 0; kc < KC; ++kc) chunk(kc, B.next[0]);
   } else {
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) chunk(kc, nh[kc % PD], nl[kc % PD]);
+    for (int kc = 0; kc < KC; ++kc) chunk(kc, B.next[kc % PD]);
   }
 }
 
@@ -161,26 +192,9 @@ __device__ __forceinline__ void wave_mm_rows(const float *act, int ld, int rbs, 
   }
 }
 
-// Row blocks stacked contiguously: block rb starts 16 rows after block rb - 1.
-template <int RB, int NB>
-__device__ __forceinline__ void wave_mm_rb(const float *act, int ld, int Kin, const float *__restrict__ Bt, int col0,
-                                           floatx4 (&acc)[RB][NB]) {
-  wave_mm_rows<RB, NB>(act, ld, 16 * ld, Kin, Bt, col0, acc);
-}
-
-// wave_mm_rb with the operands of each instruction swapped: the accumulator holds the product
-// transposed.  Entry t of acc[rb][cb] in lane l is D_rb[l%16][col0 + cb*16 + 4(l/16) + t], so a
-// lane holds four consecutive columns of one row, which a row-major store or load moves in one
-// vector access.  Same products, same k order.
-template <int RB, int NB>
-__device__ __forceinline__ void wave_mm_t(const float *act, int ld, int Kin, const float *__restrict__ Bt, int col0,
-                                          floatx4 (&acc)[RB][NB]) {
-  wave_mm_rows<RB, NB, true>(act, ld, 16 * ld, Kin, Bt, col0, acc);
-}
-
 // The same product with this wave's weight fragments already in registers: b[kc][cb] holds
 // Bt[col0 + cb*16 + l%16][16 kc + 4(l/16) .. +3] for the KC = Kin/16 chunks (TR: transposed
-// accumulator, as wave_mm_t).
+// accumulator, as mfma4_ab).
 template <int RB, int NB, int KC, bool TR = false>
 __device__ __forceinline__ void wave_mm_rows_breg(const float *act, int ld, int rbs, const float4 (&b)[KC][NB],
                                                   floatx4 (&acc)[RB][NB]) {

@@ -311,14 +311,13 @@ __global__ void __launch_bounds__(kMolThreads) k_mol_setup(MolCall c) {
     a->pf.z1[l] = w.z1[l];
     a->pf.z2[l] = w.z2[l];
     a->pf.z3[l] = w.z3[l];
-    a->pf.h[l] = nullptr;   // not stored: the message gathers form h from z3 and phi
     a->pb.z1[l] = w.z1[l];
     a->pb.z2[l] = w.z2[l];
     a->pb.z3[l] = w.z3[l];
     a->pfb.z1[l] = reinterpret_cast<__bf16 *>(w.z1[l]);
     a->pfb.z2[l] = reinterpret_cast<__bf16 *>(w.z2[l]);
     a->pfb.z3[l] = reinterpret_cast<__bf16 *>(w.z3[l]);
-    a->pfb.h[l] = nullptr;
+    a->pfb.h[l] = nullptr;   // not stored: the message gathers form h from z3 and phi
     a->pbb.z1[l] = reinterpret_cast<const __bf16 *>(w.z1[l]);
     a->pbb.z2[l] = reinterpret_cast<const __bf16 *>(w.z2[l]);
     a->pbb.z3[l] = reinterpret_cast<const __bf16 *>(w.z3[l]);
@@ -457,7 +456,7 @@ __global__ void __launch_bounds__(kMolThreads, 1)
       if constexpr (BF16)
         pair_fwd_tile_bf16<F, K, kMolRB>(a.pfb, p0, nv);
       else
-        pair_fwd_tile_split<F, K, kMolRB, 4>(a.pf, p0, nv, smem);
+        pair_fwd_tile<F, K, kMolRB, 4>(a.pf, p0, nv, smem);
       __syncthreads();
     }
     // ---- embedding gather (G waves per atom, 4 / G atoms at a time)
@@ -728,7 +727,7 @@ __global__ void __launch_bounds__(kMolThreads, 1)
       if constexpr (BF16)
         pair_bwd_tile_bf16<F, K, kMolRB>(a.pbb, p0, nv);
       else
-        pair_bwd_tile_split<F, K, kMolRB, 4, 2>(a.pb, p0, nv, smem);
+        pair_bwd_tile<F, K, kMolRB, 4, 2>(a.pb, p0, nv, smem);
       __syncthreads();
     }
     // ---- forces: per-atom sums of the pair gradients in FP64
@@ -738,30 +737,6 @@ __global__ void __launch_bounds__(kMolThreads, 1)
     });
     __syncthreads();
   }
-}
-
-// The molecule kernel's pair tiles take split operands, so the FP32 evaluation of a model without
-// split weights (SplitPlan) runs the fused path's launches.
-inline bool runs_fused(const tn_model *m, int prec) { return prec == TN_FP32 && !m->split.ok; }
-
-// The molecule path's pair budget is split over the systems: flags one that exceeds its share.
-__global__ void k_share_overflow(int64_t N, int64_t S, int64_t max_pairs, const int32_t *__restrict__ batch,
-                                 const int32_t *__restrict__ rowptr, const int64_t *__restrict__ n_pairs, int64_t MP,
-                                 int32_t *status) {
-  const int64_t sys = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (sys >= S || *n_pairs > MP) return;   // past the whole budget there are no rows (and the flag is set)
-  auto first = [&](int32_t v) {   // first atom whose system is at least v
-    int64_t lo = 0, hi = N;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (batch[mid] < v) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-  };
-  const int64_t a0 = first((int32_t)sys), a1 = first((int32_t)sys + 1);
-  if (a1 <= a0) return;
-  const int64_t pr0 = (max_pairs * a0 / N + 15) / 16 * 16, pr1 = (max_pairs * a1 / N + 15) / 16 * 16;
-  if ((rowptr[a1] - rowptr[a0]) / 2 > pr1 - pr0) set_status(status, TN_STATUS_OVERFLOW);
 }
 
 template <int F, int K, bool BF16>
@@ -785,8 +760,6 @@ size_t molecule_workspace_bytes(const tn_model *m, int64_t n, int64_t S, int64_t
   if ((prec != TN_FP32 && prec != TN_BF16) || !molecule_kernels_support(m->F, m->K, prec == TN_BF16) ||
       m->L > kMaxLayers)
     return 0;
-  if (runs_fused(m, prec))
-    return fused_workspace_bytes(m, n, S, mol_pair_capacity(max_pairs), BoxInfo(), prec, want_forces);
   WsPlan p(nullptr);
   if (prec == TN_BF16) {
     MolWs<float> w;
@@ -806,19 +779,6 @@ int molecule_run(const tn_model *m, hipStream_t s, const Problem &pb, int prec, 
   const int64_t N = pb.n, MP = mol_pair_capacity(pb.max_pairs), F = m->F, L = m->L;
   if (2 * MP >= (int64_t(1) << 31)) return TN_E_ARG;   // CSR offsets are int32
   if (!m->mol_const) return TN_E_UNSUPPORTED;
-  if (runs_fused(m, prec)) {
-    Problem fpb = pb;
-    fpb.max_pairs = MP;
-    int rc = fused_run(m, s, fpb, prec, ws, ws_bytes);
-    if (rc || N <= 0 || pb.S <= 0) return rc;
-    WsPlan plan(ws);
-    NbrWs nb;   // the fused path's first buffers: its row offsets
-    plan_neighbors(plan, N, MP, pb.box, &nb);
-    hipLaunchKernelGGL(k_share_overflow, dim3(grid_for(pb.S, 256)), dim3(256), 0, s, N, pb.S, pb.max_pairs, pb.batch,
-                       nb.deg, pb.n_pairs, MP, pb.status);
-    TN_LAUNCH_CHECK();
-    return TN_OK;
-  }
   auto go = [&](auto ta) -> int {
   using TA = decltype(ta);
   WsPlan plan(ws);
@@ -918,24 +878,16 @@ int molecule_setup(tn_model *m) {
   model_fields(h.pbb);
   gather_fields(h.pb.g);
   gather_fields(h.pbb.g);
-  h.pf.W0 = W(o.W0f);
   h.pf.b0 = W(o.b0);
   h.pf.b0lo = W(o.b0lo);
-  h.pb.W0T = W(o.W0T);
   h.pfb.W0 = WB(o.W0f);
   h.pfb.b0 = W(o.b0);
   h.pbb.W0T = WB(o.W0T);
   for (int64_t l = 0; l < L; ++l) {
     const LayerOff &lo = o.layer[l];
-    h.pf.Wa[l] = W(lo.Waf);
     h.pf.ba[l] = W(lo.ba);
-    h.pf.Wb[l] = W(lo.Wbf);
     h.pf.bb[l] = W(lo.bb);
-    h.pf.Wc[l] = W(lo.Wcf);
     h.pf.bc[l] = W(lo.bc);
-    h.pb.WaT[l] = W(lo.WaT);
-    h.pb.WbT[l] = W(lo.WbT);
-    h.pb.WcT[l] = W(lo.WcT);
     h.pfb.Wa[l] = WB(lo.Waf);
     h.pfb.Wb[l] = WB(lo.Wbf);
     h.pfb.Wc[l] = WB(lo.Wcf);
@@ -948,16 +900,14 @@ int molecule_setup(tn_model *m) {
   }
   split_args(m, h.pf);
   split_args(m, h.pb);
-  if (m->split.ok) {
-    wt.mix = split_mix(m, m->split.mix);
-    wt.mixT = split_mix(m, m->split.mixT);
-    for (int64_t l = 0; l < L; ++l) {
-      const SplitLayer &sl = m->split.layer[l];
-      wt.W1s[l] = split_mix(m, sl.W1);
-      wt.W1Ts[l] = split_mix(m, sl.W1T);
-      wt.W2s[l] = split_mix(m, sl.W2);
-      wt.W2Ts[l] = split_mix(m, sl.W2T);
-    }
+  wt.mix = split_mix(m, m->split.mix);
+  wt.mixT = split_mix(m, m->split.mixT);
+  for (int64_t l = 0; l < L; ++l) {
+    const SplitLayer &sl = m->split.layer[l];
+    wt.W1s[l] = split_mix(m, sl.W1);
+    wt.W1Ts[l] = split_mix(m, sl.W1T);
+    wt.W2s[l] = split_mix(m, sl.W2);
+    wt.W2Ts[l] = split_mix(m, sl.W2T);
   }
   TN_HIP(hipMalloc(&m->mol_const, sizeof(MolConst)));
   TN_HIP(hipMemcpy(m->mol_const, &h, sizeof(MolConst), hipMemcpyHostToDevice));

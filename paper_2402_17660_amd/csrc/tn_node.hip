@@ -66,10 +66,7 @@ int launch_node_bwd(hipStream_t s, int F, bool top, bool bottom, const NodeBwdAr
 
 MixSplit split_mix(const tn_model *m, const SplitMix &x) {
   MixSplit r;
-  for (int p = 0; p < 3; ++p) {
-    r.W[p] = m->wsplit + x.at[p];
-    r.s[p] = x.s[p];
-  }
+  for (int p = 0; p < 3; ++p) r.W[p] = m->wsplit + x.at[p];
   return r;
 }
 

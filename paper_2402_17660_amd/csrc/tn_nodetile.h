@@ -20,8 +20,7 @@
 // at F = 128, of which the maps and staging about half, the mixings' weights the rest; the small
 // tile takes 11.5 us (a call 370 -> 291 us).
 //
-// The mixings run on split operands (tn_mfma.h).  An operand row (one coordinate of one atom) is
-// scaled by the power of two of the largest entry of its part (I, A or S) in that atom.
+// The mixings run on split operands (tn_mfma.h).
 #pragma once
 
 #include "tn_internal.h"
@@ -30,10 +29,9 @@
 
 namespace tn {
 
-// One mixing's three matrices as split weights, and the factors that take their scales off.
+// One mixing's three matrices as split weights.
 struct MixSplit {
-  const _Float16 *W[3] = {nullptr, nullptr, nullptr};
-  float s[3] = {0, 0, 0};
+  const __bf16 *W[3] = {nullptr, nullptr, nullptr};
 };
 
 struct NodeFwdArgs {
@@ -205,44 +203,30 @@ __device__ __forceinline__ void std_(double *p, const double (&o)[V]) {
 }
 
 // ---------------------------------------------------------------- the tile
-// The power of two that a part of an atom is scaled by, and its inverse, from the bits of its largest
-// magnitude.
-__device__ __forceinline__ void split_scale(int top, float &sc, float &inv) {
-  int e = top >> 23;
-  e = e < 15 ? 15 : e;
-  sc = __builtin_bit_cast(float, (268 - e) << 23);
-  inv = __builtin_bit_cast(float, (e - 14) << 23);
-}
-
 // NW waves; wave w holds channels [w F / NW, (w + 1) F / NW) in NB blocks of 16, lane l of block cb
 // the channels cb*16 + 4(l/16) .. +3 of atom l%16.
 template <int F, int WAVES>
 struct NodeTile {
   static constexpr int NW = WAVES;
-  static constexpr int NB = F / (16 * NW), KC = F / 32, LD = F + kPadH, LO = 9 * 16 * LD;
+  static constexpr int NB = F / (16 * NW), KC = F / 32, LD = F + kPadH, PL = 9 * 16 * LD;
   static_assert(F % (16 * NW) == 0 && F % 32 == 0, "whole blocks per wave");
-  static constexpr size_t bytes = 2 * LO * sizeof(_Float16) + 2 * 48 * sizeof(int) + 2 * F * sizeof(double);
+  static constexpr size_t bytes = 3 * PL * sizeof(__bf16) + 2 * F * sizeof(double);
   static constexpr int TA = 16, VT = 4;   // atoms; channels of a lane in a block
   static constexpr bool kEarly = false;
   using Feat = floatx4[9][NB];
   struct Frags {};
   __device__ __forceinline__ void weights(const MixSplit &, Frags &) const {}
 
-  _Float16 *sA;
+  __bf16 *sA;
   double *sSum;  // [2][16 atoms][F / 16]
-  int *sMax;     // [2][3 parts][16 atoms]: the mixing under way, the next one (cleared)
-  int wave, r16, q, phase;
+  int wave, r16, q;
 
   __device__ __forceinline__ explicit NodeTile(char *smem) {
-    sA = reinterpret_cast<_Float16 *>(smem);
-    sMax = reinterpret_cast<int *>(smem + 2 * LO * sizeof(_Float16));
-    sSum = reinterpret_cast<double *>(smem + 2 * LO * sizeof(_Float16) + 2 * 48 * sizeof(int));
+    sA = reinterpret_cast<__bf16 *>(smem);
+    sSum = reinterpret_cast<double *>(smem + 3 * PL * sizeof(__bf16));
     wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     r16 = threadIdx.x & 15;
     q = (threadIdx.x & 63) >> 4;
-    phase = 0;
-    for (int t = threadIdx.x; t < 96; t += 64 * NW) sMax[t] = 0;
-    __syncthreads();
   }
   __device__ __forceinline__ int col(int cb) const { return (wave * NB + cb) * 16 + 4 * q; }
   // rows past the last atom read it again and are not stored
@@ -282,55 +266,26 @@ struct NodeTile {
     return v;
   }
 
-  // x to LDS as split operands, scaled; inv: what takes the scale off again, per part
-  __device__ __forceinline__ void stage(const Feat &x, float (&inv)[3]) {
-    int *cur = sMax + 48 * (phase & 1), *next = sMax + 48 * (~phase & 1);
-    ++phase;
-    int top[3] = {0, 0, 0};
+  // x to LDS as split operands
+  __device__ __forceinline__ void stage(const Feat &x) {
+    __syncthreads();   // the last mixing has read sA
 #pragma unroll
     for (int c = 0; c < 9; ++c)
 #pragma unroll
-      for (int cb = 0; cb < NB; ++cb)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int b = __builtin_bit_cast(int, (float)x[c][cb][t]) & 0x7fffffff;
-          top[coord_part(c)] = b > top[coord_part(c)] ? b : top[coord_part(c)];
-        }
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      int o = __shfl_xor(top[p], 16, 64);
-      top[p] = o > top[p] ? o : top[p];
-      o = __shfl_xor(top[p], 32, 64);
-      top[p] = o > top[p] ? o : top[p];
-      if (q == 0) atomicMax(&cur[16 * p + r16], top[p]);
-    }
-    __syncthreads();   // every wave's maximum; the last mixing has read sA
-    if (threadIdx.x < 48) next[threadIdx.x] = 0;
-    float sc[3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      split_scale(cur[16 * p + r16], sc[p], inv[p]);
-    }
-#pragma unroll
-    for (int c = 0; c < 9; ++c)
-#pragma unroll
-      for (int cb = 0; cb < NB; ++cb) st4_split(sA + (c * 16 + r16) * LD + col(cb), LO, x[c][cb] * sc[coord_part(c)]);
+      for (int cb = 0; cb < NB; ++cb) st4_split(sA + (c * 16 + r16) * LD + col(cb), PL, x[c][cb]);
     __syncthreads();
   }
   // y = the staged operand times the part's matrix
-  __device__ __forceinline__ void product(const MixSplit &m, const float (&inv)[3], const Frags &, Feat &y) const {
+  __device__ __forceinline__ void product(const MixSplit &m, const Frags &, Feat &y) const {
     const int lane = threadIdx.x & 63;
-    const _Float16 *ap = sA + r16 * LD + 8 * q;
-    half8 nh[3][NB], nl[3][NB];
+    const __bf16 *ap = sA + r16 * LD + 8 * q;
+    Frag3 next[3][NB];
     auto weights = [&](int kc) {
 #pragma unroll
       for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) {
-          const _Float16 *b = m.W[p] + (size_t)((wave * NB + cb) * KC + kc) * 1024 + lane * 8;
-          nh[p][cb] = *reinterpret_cast<const half8 *>(b);
-          nl[p][cb] = *reinterpret_cast<const half8 *>(b + 512);
-        }
+        for (int cb = 0; cb < NB; ++cb)
+          next[p][cb] = ld_frag3(m.W[p] + (size_t)((wave * NB + cb) * KC + kc) * kSplitBlock + lane * 8, 512);
     };
     weights(0);
 #pragma unroll
@@ -339,32 +294,15 @@ struct NodeTile {
       for (int cb = 0; cb < NB; ++cb) y[c][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
-      half8 bh[3][NB], bl[3][NB];
+      Frag3 w[3][NB];
 #pragma unroll
       for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int cb = 0; cb < NB; ++cb) {
-          bh[p][cb] = nh[p][cb];
-          bl[p][cb] = nl[p][cb];
-        }
+        for (int cb = 0; cb < NB; ++cb) w[p][cb] = next[p][cb];
       if (kc + 1 < KC) weights(kc + 1);
 #pragma unroll
-      for (int c = 0; c < 9; ++c) {
-        const int p = coord_part(c);
-        const half8 ah = *reinterpret_cast<const half8 *>(ap + c * 16 * LD + 32 * kc);
-        const half8 al = *reinterpret_cast<const half8 *>(ap + c * 16 * LD + 32 * kc + LO);
-#pragma unroll
-        for (int cb = 0; cb < NB; ++cb) y[c][cb] = mfma_f16(bl[p][cb], ah, y[c][cb]);
-#pragma unroll
-        for (int cb = 0; cb < NB; ++cb) y[c][cb] = mfma_f16(bh[p][cb], al, y[c][cb]);
-#pragma unroll
-        for (int cb = 0; cb < NB; ++cb) y[c][cb] = mfma_f16(bh[p][cb], ah, y[c][cb]);
-      }
+      for (int c = 0; c < 9; ++c) mfma_split(w[coord_part(c)], ld_frag3(ap + c * 16 * LD + 32 * kc, PL), y[c]);
     }
-#pragma unroll
-    for (int c = 0; c < 9; ++c)
-#pragma unroll
-      for (int cb = 0; cb < NB; ++cb) y[c][cb] = y[c][cb] * inv[coord_part(c)] * m.s[coord_part(c)];
   }
 };
 
@@ -376,34 +314,29 @@ struct NodeTile {
 // staged (a lone tile otherwise waits for the memory-side cache at every chunk).
 template <int F>
 struct NodeTileSmall {
-  static constexpr int TA = 4, VT = 1, NB = 1, NW = TA * F / 64, KC = F / 32, LD = F + kPadH, LO = 64 * LD, LDY = F + 4;
+  static constexpr int TA = 4, VT = 1, NB = 1, NW = TA * F / 64, KC = F / 32, LD = F + kPadH, PL = 64 * LD, LDY = F + 4;
   static_assert(16 * NW == F && F % 64 == 0, "a wave per 16 columns, whole waves per atom");
   static constexpr bool kEarly = true;
-  static constexpr size_t bytes = 2 * LO * sizeof(_Float16) + 64 * LDY * sizeof(float) + 2 * 3 * TA * sizeof(int) + 2 * TA * (F / 16) * sizeof(double);
+  static constexpr size_t bytes = 3 * PL * sizeof(__bf16) + 64 * LDY * sizeof(float) + 2 * TA * (F / 16) * sizeof(double);
   using Feat = float[9][1][1];
   struct Frags {
-    half8 h[KC][3], l[KC][3];
+    Frag3 w[KC][3];
   };
 
-  _Float16 *sA;
+  __bf16 *sA;
   float *sY;
   double *sSum;  // [2][TA][F / 16]
-  int *sMax;     // [2][3 parts][TA]
-  int wave, atom, ch, phase;
+  int wave, atom, ch;
 
   __device__ __forceinline__ explicit NodeTileSmall(char *smem) {
-    sA = reinterpret_cast<_Float16 *>(smem);
-    smem += 2 * LO * sizeof(_Float16);
+    sA = reinterpret_cast<__bf16 *>(smem);
+    smem += 3 * PL * sizeof(__bf16);
     sY = reinterpret_cast<float *>(smem);
     smem += 64 * LDY * sizeof(float);
     sSum = reinterpret_cast<double *>(smem);
-    sMax = reinterpret_cast<int *>(smem + 2 * TA * (F / 16) * sizeof(double));
     wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     atom = wave * 64 / F;
     ch = threadIdx.x % F;
-    phase = 0;
-    if (threadIdx.x < 6 * TA) sMax[threadIdx.x] = 0;
-    __syncthreads();
   }
   __device__ __forceinline__ int col(int) const { return ch; }
   __device__ __forceinline__ bool live(int navail) const { return atom < navail; }
@@ -434,36 +367,10 @@ struct NodeTileSmall {
     for (int b = 0; b < F / 16; ++b) v += s[b];
     return v;
   }
-  __device__ __forceinline__ void stage(const Feat &x, float (&inv)[3]) {
-    int *cur = sMax + 3 * TA * (phase & 1), *next = sMax + 3 * TA * (~phase & 1);
-    ++phase;
-    int top[3] = {0, 0, 0};
+  __device__ __forceinline__ void stage(const Feat &x) {
+    __syncthreads();   // the last mixing has read sA
 #pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      const int b = __builtin_bit_cast(int, x[c][0][0]) & 0x7fffffff;
-      top[coord_part(c)] = b > top[coord_part(c)] ? b : top[coord_part(c)];
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-#pragma unroll
-      for (int m = 1; m < 16; m *= 2) {
-        const int o = __shfl_xor(top[p], m, 64);
-        top[p] = o > top[p] ? o : top[p];
-      }
-      if (ch % 16 == 0) atomicMax(&cur[TA * p + atom], top[p]);
-    }
-    __syncthreads();   // every wave's maximum; the last mixing has read sA
-    if (threadIdx.x < 3 * TA) next[threadIdx.x] = 0;
-    float sc[3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) split_scale(cur[TA * p + atom], sc[p], inv[p]);
-#pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      const float v = x[c][0][0] * sc[coord_part(c)];
-      const _Float16 h = (_Float16)v;
-      sA[at(c) * LD + ch] = h;
-      sA[at(c) * LD + ch + LO] = (_Float16)(v - (float)h);
-    }
+    for (int c = 0; c < 9; ++c) st_split<1>(sA + at(c) * LD + ch, PL, x[c][0]);
     __syncthreads();
   }
   __device__ __forceinline__ void weights(const MixSplit &m, Frags &f) const {
@@ -471,38 +378,28 @@ struct NodeTileSmall {
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        const _Float16 *b = m.W[p] + (size_t)(wave * KC + kc) * 1024 + lane * 8;
-        f.h[kc][p] = *reinterpret_cast<const half8 *>(b);
-        f.l[kc][p] = *reinterpret_cast<const half8 *>(b + 512);
-      }
+      for (int p = 0; p < 3; ++p)
+        f.w[kc][p] = ld_frag3(m.W[p] + (size_t)(wave * KC + kc) * kSplitBlock + lane * 8, 512);
   }
-  __device__ __forceinline__ void product(const MixSplit &m, const float (&inv)[3], const Frags &f, Feat &y) const {
+  __device__ __forceinline__ void product(const MixSplit &, const Frags &f, Feat &y) const {
     const int r16 = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
-    const _Float16 *ap = sA + r16 * LD + 8 * q;
-    floatx4 acc[4];
+    const __bf16 *ap = sA + r16 * LD + 8 * q;
+    floatx4 acc[4][1];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) acc[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < 4; ++rb) acc[rb][0] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
-      half8 h[4], l[4];
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb) {
-        h[rb] = *reinterpret_cast<const half8 *>(ap + rb * 16 * LD + 32 * kc);
-        l[rb] = *reinterpret_cast<const half8 *>(ap + rb * 16 * LD + 32 * kc + LO);
+        const Frag3 w[1] = {f.w[kc][rb < 2 ? rb : 2]};
+        mfma_split(w, ld_frag3(ap + rb * 16 * LD + 32 * kc, PL), acc[rb]);
       }
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_f16(f.l[kc][rb < 2 ? rb : 2], h[rb], acc[rb]);
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_f16(f.h[kc][rb < 2 ? rb : 2], l[rb], acc[rb]);
-#pragma unroll
-      for (int rb = 0; rb < 4; ++rb) acc[rb] = mfma_f16(f.h[kc][rb < 2 ? rb : 2], h[rb], acc[rb]);
     }
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) st4(sY + (rb * 16 + r16) * LDY + wave * 16 + 4 * q, acc[rb]);
+    for (int rb = 0; rb < 4; ++rb) st4(sY + (rb * 16 + r16) * LDY + wave * 16 + 4 * q, acc[rb][0]);
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 9; ++c) y[c][0][0] = sY[at(c) * LDY + ch] * inv[coord_part(c)] * m.s[coord_part(c)];
+    for (int c = 0; c < 9; ++c) y[c][0][0] = sY[at(c) * LDY + ch];
   }
 };
 
@@ -534,7 +431,6 @@ __device__ __forceinline__ void node_fwd_tile(NT &nt, const NodeFwdArgs &a, int6
   const int64_t i = nt.row(a0, navail);
   typename NT::Feat x, y, z;
   typename NT::Frags w;
-  float inv[3];
   double g[FIRST ? NB : 1][3][VT];
   auto operands = [&]() {   // what the first mixing's result meets
     if constexpr (!FIRST) {
@@ -549,9 +445,9 @@ __device__ __forceinline__ void node_fwd_tile(NT &nt, const NodeFwdArgs &a, int6
   nt.load(a.in, i, x);
   nt.weights(a.A, w);
   if constexpr (NT::kEarly) operands();
-  nt.stage(x, inv);
+  nt.stage(x);
   if constexpr (!NT::kEarly && !FIRST) operands();
-  nt.product(a.A, inv, w, y);
+  nt.product(a.A, w, y);
   if constexpr (!LAST) nt.weights(a.B, w);
   nt.store(a.mid, i, navail, y);
   if constexpr (!NT::kEarly && FIRST) operands();
@@ -629,8 +525,8 @@ __device__ __forceinline__ void node_fwd_tile(NT &nt, const NodeFwdArgs &a, int6
 #pragma unroll
       for (int c = 0; c < 9; ++c) v[c] = (float)u[c].v;
     });
-    nt.stage(x, inv);
-    nt.product(a.B, inv, w, y);
+    nt.stage(x);
+    nt.product(a.B, w, y);
     nt.store(a.Y, i, navail, y);
   }
 }
@@ -641,7 +537,6 @@ __device__ __forceinline__ void node_bwd_tile(NT &nt, const NodeBwdArgs &a, int6
   const int64_t i = nt.row(a0, navail);
   typename NT::Feat x, y, z, u, d0, y0, m0;
   typename NT::Frags w;
-  float inv[3];
   auto below = [&]() {   // of the layer below
     if constexpr (!BOTTOM) {
       nt.load(a.Y, i, y0);
@@ -710,9 +605,9 @@ __device__ __forceinline__ void node_bwd_tile(NT &nt, const NodeBwdArgs &a, int6
       mixed();
       below();
     }
-    nt.stage(x, inv);
+    nt.stage(x);
     if constexpr (!NT::kEarly) above();
-    nt.product(a.A, inv, w, y);
+    nt.product(a.A, w, y);
     nt.weights(a.B, w);
     channels<NT>(x, [&](int cb, int t, float (&v)[9]) {
       float p[9], q[9], e[9];
@@ -752,8 +647,8 @@ __device__ __forceinline__ void node_bwd_tile(NT &nt, const NodeBwdArgs &a, int6
         for (int t = 0; t < VT; ++t) s[t] *= silu_grad(ez[t]);
         if (nt.live(navail)) std_<VT>(a.dez + o, s);
       }
-    nt.stage(x, inv);
-    nt.product(a.B, inv, w, y);
+    nt.stage(x);
+    nt.product(a.B, w, y);
     nt.store(a.dXr, i, navail, y);
   } else {
     nt.store(a.dX, i, navail, x);
@@ -762,9 +657,9 @@ __device__ __forceinline__ void node_bwd_tile(NT &nt, const NodeBwdArgs &a, int6
       channel<NT>(d0, cb, t, d);
       residual_bwd_channel(d, v);
     });
-    nt.stage(x, inv);
+    nt.stage(x);
     if constexpr (!NT::kEarly) below();
-    nt.product(a.B, inv, w, y);
+    nt.product(a.B, w, y);
     channels<NT>(y, [&](int cb, int t, float (&v)[9]) {
       float yc[9], mc[9];
       channel<NT>(y0, cb, t, yc);
@@ -787,7 +682,7 @@ constexpr int node_waves(int F) { return F / 16; }
 int launch_node_fwd(hipStream_t s, int F, bool first, bool last, const NodeFwdArgs &a);
 int launch_node_bwd(hipStream_t s, int F, bool top, bool bottom, const NodeBwdArgs &a);
 
-// A mixing's split weights: q-th of the sets below.
+// A mixing's split weights.
 MixSplit split_mix(const tn_model *m, const SplitMix &x);
 
 }  // namespace tn

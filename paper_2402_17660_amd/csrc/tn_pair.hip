@@ -15,30 +15,28 @@ bool pair_kernels_support(int F, int K, int L, bool bf16) {
 // arithmetic in the same order, so results do not depend on the shape; tn_autotune picks the
 // fastest.  Pairs, waves and workgroups per CU, with the time of a launch on the 100,000-atom box
 // (2.6 M pairs) and on a 22-atom molecule (180 pairs; both F = 128, two layers):
-//   FP32 forward: 0 = 32, 4, 3 (6.6 ms, 32 us); 1 = 64 (48 for K > 32), 8, 2 (5.6 ms; F = 64: 64, 4, 2);
-//     2 = 16, 4, 4 with four chunks of weights in flight (9.6 ms, 36 us); 3 = 16, 16, 1 with three
-//     (12.6 ms, 25 us); 4 = 48, 4, 2 (6.0 ms, 38 us)
-//   FP32 reverse: 0 = 32, 4, 3 (11.7 ms, 67 us); 1 = 48, 8, 2 (11.5 ms; F = 64: 32, 4, 2); 2 = 16, 4, 2
-//     with four chunks in flight (17.7 ms, 50 us); 3 = 16, 16, 1 with three (24.6 ms, 41 us);
-//     4 = 48, 4, 2 (11.5 ms, 83 us)
+//   FP32 forward: 0 = 32, 8, 2 (9.1 ms, 37 us); 1 = 48, 4, 2 (8.3 ms, 53 us); 2 = 16, 8, 2 (13.0 ms, 26 us);
+//     3 = 16, 16, 1 with two chunks of weights in flight (16.3 ms, 26 us); 4 = 48, 8, 2 (8.4 ms, 47 us;
+//     F = 64: 32, 4, 3)
+//   FP32 reverse: 0 = 32, 4, 2 (14.5 ms, 66 us; F = 64: 48, 8, 2); 1 = 32, 8, 2 (14.6 ms, 60 us); 2 = 16, 8, 2
+//     (20.0 ms, 39 us); 3 = 16, 16, 1 with three chunks in flight (29.5 ms, 40 us); 4 = 64, 8, 1 (14.6 ms,
+//     88 us; F = 64: 32, 4, 2)
 //   BF16: 0 = 64 pairs, 4 waves, 1 per CU; 1 = 32, 4, 2; 2 = 48, 4, 2; 3, 4: below
-// With the products on FP32 instructions the best shapes took 13.7 and 18.7 ms, and 64 and 94 us;
-// those kernels remain for models without split weights (SplitPlan), in one shape.  The 22-atom figures
-// are without the reading ahead of blocks without a tile (read_ahead), with it shape 3 takes 19 and 31 us.
+// With the products on FP32 instructions the best shapes took 13.7 and 18.7 ms, and 64 and 94 us.
 int pair_variant_count(bool bf16) { return bf16 ? 5 : 5; }
 
 // The shape of a call that was neither tuned nor forced, from the pair budget (the pairs
 // themselves are known on the device only; molecules fill about half of 32 pairs per atom, boxes
-// nearly all).  A budget of up to 1.5 tiles of 16 pairs per CU is a latency chain, one tile per CU
-// and most CUs idle: sixteen waves per tile share its rows and weight loads (166 atoms, 2700
-// pairs: 27 and 42 us against 33 and 66 in shape 0, 57 in 16 pairs and four waves).  Up to 16384
-// there are one or two tiles per CU (400 atoms, 7500 pairs: 36 us forward in shape 0, 48 in 3;
-// 58 us reverse in shape 2, 69 in 0 and 80 in 3).  Beyond, the tile's reuse of each weight
-// fragment and the waves that hide its gathers decide, as at 2.6 M pairs; for F = 128 shape 0 still
-// wins up to 100,000 in reverse (198 against 217 us at 39,000 pairs, 312 against 331 at 65,000; 730
-// and 709 at 157,000) and, by the whole call (the forward's own time is the shorter in shape 1, the
-// next kernels' longer), up to 200,000 forward (1325 and 1353 us at 65,000 pairs, 2740 and 2784 at
-// 157,000; 4230 and 4216 at 270,000).  BF16, forward and
+// nearly all).  FP32: a budget of up to 1.5 tiles of 16 pairs per CU is a latency chain, one tile per CU
+// and most CUs idle: sixteen waves per tile share its rows and weight loads (166 atoms, 2700 pairs:
+// 28.9 and 46.1 us in shape 3, 28.1 and 48.3 in 2, 37 and 58 in the best of the others).  Up to 16384
+// there are one or two tiles per CU, and the fewer waves of shape 2 let two of them share one
+// (400 atoms, 7500 pairs: 47 and 64 us, 57 and 96 in shape 3, 42 and 61 in the best of the others; F = 64
+// 22.6 and 31.3, 29 and 48, 23 and 36).  Beyond, the tile's reuse of each weight fragment and the waves
+// that hide its gathers decide, as at 2.6 M pairs: forward shape 1 (800 atoms, 20,900 pairs: 85 us, 96 in
+// 0 and 125 in 2; 6000 atoms 496, 552 in 0; F = 64 182, 225 in 0), reverse shape 1 (136 us, 144 in 0
+// and 183 in 2; 904 and 926 in 0), and shape 0 for F = 64 (343 us, 396 in 1; 800 atoms 54 and 68).
+// BF16, forward and
 // reverse: 35 and 51 us in shape 1 at 180 pairs (38 and 75 in 0); 4.0 and 8.6 ms in shapes 4 and
 // 3 at 2.6 M pairs (5.6 and 12.1 in 0), shape 3 forward below 100,000 (132 against 145 us at
 // 65,000); for F = 64 shapes 2 and 1 (575 and 1203 us at 785,000 pairs, 582 and 1402 in 0).
@@ -49,8 +47,8 @@ int pair_default_variant(int F, bool bf16, int64_t max_pairs, bool reverse) {
     return reverse || max_pairs <= 100000 ? 3 : 4;
   }
   if (max_pairs <= 6144) return 3;
-  if (max_pairs <= 16384) return reverse ? 2 : 0;
-  return F == 128 && max_pairs <= (reverse ? 100000 : 200000) ? 0 : 1;
+  if (max_pairs <= 16384) return 2;
+  return !reverse || F == 128 ? 1 : 0;
 }
 
 template <int TILE>
@@ -58,42 +56,22 @@ static unsigned tile_grid(int64_t max_pairs) {
   return (unsigned)((max_pairs + TILE - 1) / TILE);
 }
 
-template <int F, int K, int RB, int NW, int MINB>
+template <int F, int K, int RB, int NW, int MINB, int PD = 1>
 static int launch_fwd_v(hipStream_t s, const PairFwdArgs &a) {
   const unsigned grid = tile_grid<16 * RB>(a.max_pairs);
   if (grid == 0) return TN_OK;
   TimedScope ts("edge_fwd", s);
-  hipLaunchKernelGGL((k_pair_fwd<F, K, RB, NW, MINB>), dim3(grid), dim3(64 * NW), 0, s, a);
+  hipLaunchKernelGGL((k_pair_fwd<F, K, RB, NW, MINB, PD>), dim3(grid), dim3(64 * NW), 0, s, a);
   TN_LAUNCH_CHECK();
   return TN_OK;
 }
 
-template <int F, int K, int RB, int NW, int MINB>
+template <int F, int K, int RB, int NW, int MINB, int PD = 1>
 static int launch_bwd_v(hipStream_t s, const PairBwdArgs &a) {
   const unsigned grid = tile_grid<16 * RB>(a.max_pairs);
   if (grid == 0) return TN_OK;
   TimedScope ts("edge_bwd", s);
-  hipLaunchKernelGGL((k_pair_bwd<F, K, RB, NW, MINB>), dim3(grid), dim3(64 * NW), 0, s, a);
-  TN_LAUNCH_CHECK();
-  return TN_OK;
-}
-
-template <int F, int K, int RB, int NW, int MINB, int PD = 1>
-static int launch_fwd_split_v(hipStream_t s, const PairFwdArgs &a) {
-  const unsigned grid = tile_grid<16 * RB>(a.max_pairs);
-  if (grid == 0) return TN_OK;
-  TimedScope ts("edge_fwd", s);
-  hipLaunchKernelGGL((k_pair_fwd_split<F, K, RB, NW, MINB, PD>), dim3(grid), dim3(64 * NW), 0, s, a);
-  TN_LAUNCH_CHECK();
-  return TN_OK;
-}
-
-template <int F, int K, int RB, int NW, int MINB, int PD = 1>
-static int launch_bwd_split_v(hipStream_t s, const PairBwdArgs &a) {
-  const unsigned grid = tile_grid<16 * RB>(a.max_pairs);
-  if (grid == 0) return TN_OK;
-  TimedScope ts("edge_bwd", s);
-  hipLaunchKernelGGL((k_pair_bwd_split<F, K, RB, NW, MINB, PD>), dim3(grid), dim3(64 * NW), 0, s, a);
+  hipLaunchKernelGGL((k_pair_bwd<F, K, RB, NW, MINB, PD>), dim3(grid), dim3(64 * NW), 0, s, a);
   TN_LAUNCH_CHECK();
   return TN_OK;
 }
@@ -120,27 +98,25 @@ static int launch_bwd_bf16_v(hipStream_t s, const PairBwdArgsB &a) {
 
 template <int F, int K>
 static int launch_fwd(hipStream_t s, const PairFwdArgs &a, int v) {
-  if (!a.sW0) return launch_fwd_v<F, K, 2, 4, 3>(s, a);
   constexpr bool wide = F == 128;
   switch (v) {
-    case 1: return launch_fwd_split_v<F, K, (wide && K > 32) ? 3 : 4, wide ? 8 : 4, wide ? 4 : 2>(s, a);
-    case 2: return launch_fwd_split_v<F, K, 1, 4, 1, 4>(s, a);
-    case 3: return launch_fwd_split_v<F, K, 1, 16, 4, 3>(s, a);
-    case 4: return launch_fwd_split_v<F, K, 3, 4, 2>(s, a);
-    default: return launch_fwd_split_v<F, K, 2, 4, 3>(s, a);
+    case 1: return launch_fwd_v<F, K, 3, 4, 2>(s, a);
+    case 2: return launch_fwd_v<F, K, 1, 8, 4>(s, a);
+    case 3: return launch_fwd_v<F, K, 1, 16, 4, 2>(s, a);
+    case 4: return launch_fwd_v<F, K, wide ? 3 : 2, wide ? 8 : 4, wide ? 4 : 3>(s, a);
+    default: return launch_fwd_v<F, K, 2, 8, 4>(s, a);
   }
 }
 
 template <int F, int K>
 static int launch_bwd(hipStream_t s, const PairBwdArgs &a, int v) {
-  if (!a.sW0T) return launch_bwd_v<F, K, 2, 4, 3>(s, a);
   constexpr bool wide = F == 128;
   switch (v) {
-    case 1: return launch_bwd_split_v<F, K, wide ? 3 : 2, wide ? 8 : 4, wide ? 4 : 2>(s, a);
-    case 2: return launch_bwd_split_v<F, K, 1, 4, 1, 4>(s, a);
-    case 3: return launch_bwd_split_v<F, K, 1, 16, 4, 3>(s, a);
-    case 4: return launch_bwd_split_v<F, K, 3, 4, 2>(s, a);
-    default: return launch_bwd_split_v<F, K, 2, 4, 3>(s, a);
+    case 1: return launch_bwd_v<F, K, 2, 8, 4>(s, a);
+    case 2: return launch_bwd_v<F, K, 1, 8, 4>(s, a);
+    case 3: return launch_bwd_v<F, K, 1, 16, 4, 3>(s, a);
+    case 4: return launch_bwd_v<F, K, wide ? 4 : 2, wide ? 8 : 4, 2>(s, a);
+    default: return launch_bwd_v<F, K, wide ? 2 : 3, wide ? 4 : 8, 2>(s, a);
   }
 }
 

@@ -1,24 +1,20 @@
-// Fused per-pair kernels on MFMA: FP32 as three products of FP16 halves (the *_split kernels; see
-// tn_mfma.h), or on v_mfma_f32_16x16x4f32 for models without split weights, and BF16.
+// Fused per-pair kernels on MFMA: FP32, its products as six products of BF16 parts (tn_mfma.h), and BF16.
 //
 // The edge filters of TensorNet (Sec. 2.1.1; exp-normal basis and SiLU of Sec. 2.4) depend
 // on the pair distance only, so every layer's filter and the embedding's K -> 3F map are
 // evaluated once per unordered pair, in one pass over pair tiles:
 //   forward   geometry + basis (FP64) -> f0 = W0 e + b0 -> per layer
 //             z1 = Wa e + ba, z2 = Wb silu(z1) + bb, z3 = Wc silu(z2) + bc, h = phi silu(z3)
-//             (h stored only when asked for: the message gathers can form it from z3)
+//             (the message gathers form h from z3; the BF16 kernel stores it when asked for)
 //   reverse   dE/df0, dE/dphi, dE/dvhat of the embedding and, per layer, dh from the two
 //             atoms' adjoint rows (gathered in the tile's prologue), then per layer
 //             dz3 = dh phi silu'(z3), dz2 = (dz3 Wc) silu'(z2), dz1 = (dz2 Wb) silu'(z1),
 //             de += dz1 Wa;  de += df0 W0;  then dE/dv from de, dE/dphi, dE/dvhat (FP64)
 // Tiles hold 16 RB pairs (RB = 1 to 7; see the launchers); the NW waves of a workgroup
 // split the output columns, each wave covering all rows in RB 16-row MFMA blocks.
-// Activations live in LDS (row padding of
-// 4 floats), weights stream from L2 as 16-byte loads.  The K index inside each 16-wide
-// chunk is permuted (lane group q takes k = 4q..4q+3) so that one 16-byte load feeds four
-// consecutive MFMAs for both operands.  The BF16 forward kernel passes the weights as the
-// instruction's first operand, so each lane ends with four consecutive output channels of one
-// pair and stores them to the row-major BF16 arrays in one 8-byte access.
+// Activations live in LDS (padded rows), weights stream from L2 as 16-byte loads.  The FP32 kernels
+// and the BF16 forward kernel pass the weights as the instruction's first operand, so each lane
+// ends with four consecutive output channels of one pair and stores them in one access.
 #pragma once
 
 #include "tn_internal.h"
@@ -46,7 +42,7 @@ __device__ __forceinline__ void for_acc_rc(const floatx4 (&acc)[RB][NB], int col
         f(rb, cb, t, rb * 16 + 4 * (lane >> 4) + t, col0 + cb * 16 + (lane & 15), acc[rb][cb][t]);
 }
 
-// Visit this lane's blocks of a transposed accumulator (wave_mm_t, wave_mm_bf16_t):
+// Visit this lane's blocks of a transposed accumulator (wave_mm_split, wave_mm_bf16 with TR):
 // f(rb, cb, row, col, v), where v (acc[rb][cb], writable) holds row `row`, columns col .. col+3.
 template <int RB, int NB, class Fn>
 __device__ __forceinline__ void for_acc_t(floatx4 (&acc)[RB][NB], int col0, Fn &&f) {
@@ -82,14 +78,6 @@ __device__ __forceinline__ floatx4 silu_and_grad4(const floatx4 &z, floatx4 &g) 
   return o;
 }
 
-// This lane's columns of a per-column vector (bias), loaded once before the products.
-template <int NB>
-__device__ __forceinline__ void load_cols(const float *v, int col0, float (&o)[NB]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int cb = 0; cb < NB; ++cb) o[cb] = v[col0 + cb * 16 + (lane & 15)];
-}
-
 // The stored pre-activations at this lane's accumulator positions (rows past nvalid read
 // row 0), issued before the product so that their latency overlaps the MFMAs.
 template <int RB, int NB, class TZ>
@@ -107,52 +95,7 @@ __device__ __forceinline__ void load_acc_rows(const TZ *z, int ldz, int64_t p0, 
     }
 }
 
-// The FP32 kernels store silu'(z1) and silu'(z2) in 16-pair blocks, column-major inside a
-// block: entry (p, c) of a C-column array sits at ((p / 16) * C + c) * 16 + p % 16.  The four
-// rows an accumulator lane holds are then one 16-byte access, and the sixteen lanes of a row
-// group cover 1 KB without gaps.  Only rows below nvalid are written; the buffers hold whole
-// blocks, so the reverse kernel may read a block's unwritten rows (their values are not used).
-template <int RB, int NB>
-__device__ __forceinline__ void store_acc_blocked(float *z, int C, int64_t p0, int nvalid, int col0,
-                                                  const floatx4 (&acc)[RB][NB]) {
-  const int lane = threadIdx.x & 63;
-  const int r = lane & 15, q = lane >> 4;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int row = rb * 16 + 4 * q;
-#pragma unroll
-    for (int cb = 0; cb < NB; ++cb) {
-      float *dst = z + ((p0 / 16 + rb) * C + col0 + cb * 16 + r) * 16 + 4 * q;
-      if (row + 3 < nvalid) {
-        *reinterpret_cast<floatx4 *>(dst) = acc[rb][cb];
-      } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-          if (row + t < nvalid) dst[t] = acc[rb][cb][t];
-      }
-    }
-  }
-}
-
-// Reads what store_acc_blocked wrote, at this lane's accumulator positions; row blocks that
-// start past nvalid are not read (zeros).
-template <int RB, int NB>
-__device__ __forceinline__ void load_acc_blocked(const float *z, int C, int64_t p0, int nvalid, int col0,
-                                                 float (&o)[RB][NB][4]) {
-  const int lane = threadIdx.x & 63;
-  const int r = lane & 15, q = lane >> 4;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < NB; ++cb) {
-      floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
-      if (rb * 16 < nvalid) v = *reinterpret_cast<const floatx4 *>(z + ((p0 / 16 + rb) * C + col0 + cb * 16 + r) * 16 + 4 * q);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) o[rb][cb][t] = v[t];
-    }
-}
-
-// The split kernels' accumulators are transposed (a lane holds four columns of one row), so they
+// The FP32 kernels' accumulators are transposed (a lane holds four columns of one row), so they
 // store silu'(z1) and silu'(z2) as the accumulator lies: 16-pair x 16-column blocks of 64 lanes x
 // 4 floats, entry (p, c) of a C-column array at ((p/16)*(C/16) + c/16)*256 + ((c%16)/4*16 + p%16)*4 + c%4.
 // A block is 1 KB without gaps, both ways.  Rows at or past nvalid are not written and, where
@@ -183,12 +126,6 @@ __device__ __forceinline__ void load_acc_blocks_t(const float *z, int C, int64_t
     }
 }
 
-// v * i + b per entry, one fused multiply-add each (so that every caller rounds alike).
-__device__ __forceinline__ floatx4 fma4(const floatx4 &v, float i, const floatx4 &b) {
-  return floatx4{__builtin_fmaf(v[0], i, b[0]), __builtin_fmaf(v[1], i, b[1]), __builtin_fmaf(v[2], i, b[2]),
-                 __builtin_fmaf(v[3], i, b[3])};
-}
-
 // Pair geometry in FP64 from the FP32 positions: unit vector, distance, cutoff and its derivative.
 struct PairGeo {
   double u[3], d, phi, dphi;
@@ -212,7 +149,7 @@ __device__ inline PairGeo pair_geometry(const float *pos, int64_t i, int64_t j, 
 
 
 // The tile functions below (pair_fwd_tile, pair_bwd_tile and their BF16 twins) declare their
-// LDS arrays themselves, so a kernel that calls one gets them in its static LDS (the split ones take
+// LDS arrays themselves, so a kernel that calls one gets them in its static LDS (the FP32 ones take
 // the caller's); a caller that runs several tiles in sequence synchronises the workgroup between them.
 // ============================================================================ forward
 // The column blocks (16 columns) of a C-column product that each of NW waves takes: NB each, for
@@ -230,11 +167,11 @@ struct WaveCols {
 // finds its XCD's L2 cold (weights come from the memory-side cache).  The grid is sized for the pair
 // budget, so there are blocks without a tile; while the tiles leave most compute units idle (256 or
 // fewer) up to eight of them per XCD that has tiles read the weights ahead of the tiles into its L2.
-// 22 atoms at F = 128 (15 tiles): forward 22.0 -> 19.2 us, reverse 38.0 -> 31.3; 48 atoms at F = 64 13.2 ->
-// 12.0 and 17.0 -> 16.0.
+// With two thirds of today's weight bytes, 22 atoms at F = 128 (15 tiles): forward 22.0 -> 19.2 us, reverse
+// 38.0 -> 31.3; 48 atoms at F = 64 13.2 -> 12.0 and 17.0 -> 16.0.
 //
-// Reads `count` halves (a multiple of 8), this block's share of them.
-__device__ __forceinline__ void read_range(const _Float16 *p, int count, int part, int parts) {
+// Reads `count` elements (a multiple of 8), this block's share of them.
+__device__ __forceinline__ void read_range(const __bf16 *p, int count, int part, int parts) {
   uint4 x = {0, 0, 0, 0};
   const int step = parts * (int)blockDim.x;
 #pragma unroll 8
@@ -255,26 +192,28 @@ __device__ __forceinline__ void read_ahead(int64_t T, Fn &&fn) {
   if (part < parts) fn(part, parts);
 }
 
-// The forward tile on split operands (tn_mfma.h): the model's own FP32 forward for weights whose
-// split is exact enough (SplitPlan); pair_fwd_tile below is for the others.  Against the FP32
-// instructions the products take a fifth of the matrix cycles, so the launch is bound by the
-// per-pair arrays it writes (7.5 KB per pair at F = 128 and two layers).  One LDS buffer holds
-// silu(z1) and then silu(z2), hi halves and lo halves, in the bytes the FP32 values took.
+// The forward tile.  One LDS buffer holds the tile's current operand, in three parts: the basis e, silu(z1),
+// silu(z2); each product keeps its result in registers until every wave has finished reading it.
+// Each thread keeps the entries of e it has computed and stages them again for every layer, so that
+// 48 pairs at F = 128 take 77 KB and two workgroups share a compute unit (a buffer of its own for e
+// would take 12 KB more); a tile of 16 pairs, for few pairs, has the room and spares the barriers.
+// Bound by the per-pair arrays it writes (7.5 KB per pair at F = 128 and two layers) and the matrix
+// instructions, about alike.
 template <int F, int K, int RB>
 struct PairFwdLds {
-  static constexpr int TILE = 16 * RB, KP = (K + 31) / 32 * 32;
-  __attribute__((aligned(16))) _Float16 E[2 * TILE * (KP + kPadH)];
-  __attribute__((aligned(16))) _Float16 A[2 * TILE * (2 * F + kPadH)];
+  static constexpr int TILE = 16 * RB, KP = (K + 31) / 32 * 32, LE = KP + kPadH;
+  static constexpr bool kOwnE = RB == 1;
+  __attribute__((aligned(16))) __bf16 A[3 * TILE * (2 * F + kPadH)];
+  __attribute__((aligned(16))) __bf16 E[kOwnE ? 3 * TILE * LE : 8];
   double D[TILE], phi[TILE];
 };
 template <int F, int K, int RB, int NW, int PD = 1>
-__device__ __forceinline__ void pair_fwd_tile_split(const PairFwdArgs &a, int64_t p0, int nvalid, char *smem) {
-  constexpr int TILE = 16 * RB, NT = 64 * NW;
-  constexpr int KP = (K + 31) / 32 * 32;
-  constexpr int LE = KP + kPadH, L1 = F + kPadH, L2 = 2 * F + kPadH;
+__device__ __forceinline__ void pair_fwd_tile(const PairFwdArgs &a, int64_t p0, int nvalid, char *smem) {
   using Lds = PairFwdLds<F, K, RB>;
+  constexpr int TILE = 16 * RB, NT = 64 * NW, KP = Lds::KP, LE = Lds::LE, L1 = F + kPadH, L2 = 2 * F + kPadH;
+  static_assert(KP <= 2 * F, "the basis fits the activations' buffer");
   Lds &lds = *reinterpret_cast<Lds *>(smem);
-  _Float16 *sE = lds.E, *sA = lds.A;
+  __bf16 *sA = lds.A, *sE = Lds::kOwnE ? lds.E : lds.A;
   double *sD = lds.D, *sPhi = lds.phi;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -296,89 +235,112 @@ __device__ __forceinline__ void pair_fwd_tile_split(const PairFwdArgs &a, int64_
     sPhi[tid] = ph;
   }
   __syncthreads();
-  for (int t = tid; t < TILE * KP; t += NT) {
-    const int row = t / KP, k = t % KP;
-    float v = 0.f;
-    if (k < K) {
-      const double x = sD[row] - a.mu[k];
-      v = (float)(sPhi[row] * exp(-a.beta[k] * x * x)) * kSplitE;
+  using C1 = WaveCols<F, NW>;
+  using C2 = WaveCols<2 * F, NW>;
+  using C3 = WaveCols<3 * F, NW>;
+  SplitWeights<C3::NB, KP / 32, PD> w0(a.W0, C3::cb0(C3::on(wave) ? wave : 0));   // (in flight during the basis)
+  // the basis, VE entries along K per thread and round (zeros past K), kept in registers
+  constexpr int VE = TILE * KP >= 4 * NT ? 4 : (TILE * KP >= 2 * NT ? 2 : 1);
+  constexpr int NE = TILE * KP / VE, IT = (NE + NT - 1) / NT;
+  float ev[IT][VE];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int t = tid + it * NT, row = t / (KP / VE), k0 = t % (KP / VE) * VE;
+#pragma unroll
+    for (int v = 0; v < VE; ++v) {
+      ev[it][v] = 0.f;
+      if (t < NE && k0 + v < K) {
+        const double x = sD[row] - a.mu[k0 + v];
+        ev[it][v] = (float)(sPhi[row] * exp(-a.beta[k0 + v] * x * x));
+      }
     }
-    const _Float16 hi = (_Float16)v;
-    sE[row * LE + k] = hi;
-    sE[TILE * LE + row * LE + k] = (_Float16)(v - (float)hi);
   }
+  auto stage_basis = [&]() {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int t = tid + it * NT, row = t / (KP / VE), k0 = t % (KP / VE) * VE;
+      if (t < NE) st_split<VE>(sE + row * LE + k0, TILE * LE, ev[it]);
+    }
+  };
+  stage_basis();
   __syncthreads();
 
-  // embedding map f0 = W0 e + b0
-  {
-    using C = WaveCols<3 * F, NW>;
-    floatx4 acc[RB][C::NB], br[C::NB], bl[C::NB];
-    if (C::on(wave)) {
-      zero_acc_rb<RB, C::NB>(acc);
-      // b0 to more than FP32: its rounding would be the same in every pair
-      load_cols_t<C::NB>(a.b0, C::col0(wave), br);
-      load_cols_t<C::NB>(a.b0lo, C::col0(wave), bl);
-      wave_mm_split<RB, C::NB, KP / 32, PD>(sE, TILE * LE, LE, a.sW0, C::cb0(wave), acc);
-      for_acc_t(acc, C::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
-        if (row < nvalid) st4(a.f0 + (p0 + row) * 3 * F + col, fma4(v, a.i0, bl[cb]) + br[cb]);
-      });
-    }
-  }
-  // bias, SiLU and its derivative of one product's accumulator: silu to sA (scaled), silu' to z
-  auto activation = [&](auto cols, auto &acc, const auto &br, float inv, float sc, int ld, float *z, int zc) {
+  // Each product's first weights are loaded before the stores of the one before it (a wave without columns
+  // loads the first wave's, which it does not use).
+  auto first = [&](auto cols) {
+    using C = decltype(cols);
+    return C::cb0(C::on(wave) ? wave : 0);
+  };
+  using Wa = SplitWeights<C1::NB, KP / 32, PD>;
+  using Wb = SplitWeights<C2::NB, F / 32, PD>;
+  using Wc = SplitWeights<C3::NB, 2 * F / 32, PD>;
+  // bias, SiLU and its derivative of one product's accumulator: silu to sA, silu' to z
+  auto activation = [&](auto cols, auto &acc, const auto &br, int ld, float *z, int zc) {
     using C = decltype(cols);
     for_acc_t(acc, C::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
       floatx4 g;
-      const floatx4 sv = silu_and_grad4(fma4(v, inv, br[cb]), g);
-      st4_split(sA + row * ld + col, TILE * ld, sv * sc);
+      st4_split(sA + row * ld + col, TILE * ld, silu_and_grad4(v + br[cb], g));
       v = g;   // all the reverse pass needs of the pre-activation, so that is what is stored
     });
     store_acc_blocks_t<RB, C::NB>(z, zc, p0, nvalid, C::cb0(wave), acc);
   };
+  // embedding map f0 = W0 e + b0
+  if (C3::on(wave)) {
+    floatx4 acc[RB][C3::NB], br[C3::NB], bl[C3::NB];
+    zero_acc_rb<RB, C3::NB>(acc);
+    // b0 to more than FP32: its rounding would be the same in every pair
+    load_cols_t<C3::NB>(a.b0, C3::col0(wave), br);
+    load_cols_t<C3::NB>(a.b0lo, C3::col0(wave), bl);
+    wave_mm_split(sE, TILE * LE, LE, w0, acc);
+    for_acc_t(acc, C3::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
+      if (row < nvalid) st4(a.f0 + (p0 + row) * 3 * F + col, (v + bl[cb]) + br[cb]);
+    });
+  }
   for (int l = 0; l < a.L; ++l) {
-    {  // z1 = Wa e + ba
-      using C = WaveCols<F, NW>;
-      floatx4 acc[RB][C::NB], br[C::NB];
-      if (C::on(wave)) {
-        zero_acc_rb<RB, C::NB>(acc);
-        load_cols_t<C::NB>(a.ba[l], C::col0(wave), br);
-        wave_mm_split<RB, C::NB, KP / 32, PD>(sE, TILE * LE, LE, a.sWa[l], C::cb0(wave), acc);
-      }
+    Wa wa(a.Wa[l], first(C1()));
+    if (!Lds::kOwnE && l > 0) {
       __syncthreads();   // the previous layer's last product has finished reading sA
-      if (C::on(wave)) activation(C(), acc, br, a.i1[l], a.s1[l], L1, a.z1[l], F);
-    }
-    __syncthreads();
-    {  // z2 = Wb silu(z1) + bb
-      using C = WaveCols<2 * F, NW>;
-      floatx4 acc[RB][C::NB], br[C::NB];
-      if (C::on(wave)) {
-        zero_acc_rb<RB, C::NB>(acc);
-        load_cols_t<C::NB>(a.bb[l], C::col0(wave), br);
-        wave_mm_split<RB, C::NB, F / 32, PD>(sA, TILE * L1, L1, a.sWb[l], C::cb0(wave), acc);
-      }
+      stage_basis();
       __syncthreads();
-      if (C::on(wave)) activation(C(), acc, br, a.i2[l], a.s2[l], L2, a.z2[l], 2 * F);
     }
+    // z1 = Wa e + ba
+    floatx4 acc1[RB][C1::NB], br1[C1::NB];
+    if (C1::on(wave)) {
+      zero_acc_rb<RB, C1::NB>(acc1);
+      load_cols_t<C1::NB>(a.ba[l], C1::col0(wave), br1);
+      wave_mm_split(sE, TILE * LE, LE, wa, acc1);
+    }
+    Wb wb(a.Wb[l], first(C2()));
+    __syncthreads();   // every wave has read e (and, with e apart, the previous layer's silu(z2))
+    if (C1::on(wave)) activation(C1(), acc1, br1, L1, a.z1[l], F);
     __syncthreads();
-    {  // z3 = Wc silu(z2) + bc
-      using C = WaveCols<3 * F, NW>;
-      floatx4 acc[RB][C::NB], br[C::NB];
-      if (C::on(wave)) {
-        zero_acc_rb<RB, C::NB>(acc);
-        load_cols_t<C::NB>(a.bc[l], C::col0(wave), br);
-        wave_mm_split<RB, C::NB, 2 * F / 32, PD>(sA, TILE * L2, L2, a.sWc[l], C::cb0(wave), acc);
-        float *z3 = a.z3[l];
-        const float i3 = a.i3[l];
-        for_acc_t(acc, C::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
-          if (row < nvalid) st4(z3 + (p0 + row) * 3 * F + col, fma4(v, i3, br[cb]));
-        });
-      }
+    // z2 = Wb silu(z1) + bb
+    floatx4 acc2[RB][C2::NB], br2[C2::NB];
+    if (C2::on(wave)) {
+      zero_acc_rb<RB, C2::NB>(acc2);
+      load_cols_t<C2::NB>(a.bb[l], C2::col0(wave), br2);
+      wave_mm_split(sA, TILE * L1, L1, wb, acc2);
+    }
+    Wc wc(a.Wc[l], first(C3()));
+    __syncthreads();
+    if (C2::on(wave)) activation(C2(), acc2, br2, L2, a.z2[l], 2 * F);
+    __syncthreads();
+    // z3 = Wc silu(z2) + bc
+    if (C3::on(wave)) {
+      floatx4 acc[RB][C3::NB], br[C3::NB];
+      zero_acc_rb<RB, C3::NB>(acc);
+      load_cols_t<C3::NB>(a.bc[l], C3::col0(wave), br);
+      wave_mm_split(sA, TILE * L2, L2, wc, acc);
+      float *z3 = a.z3[l];
+      for_acc_t(acc, C3::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
+        if (row < nvalid) st4(z3 + (p0 + row) * 3 * F + col, v + br[cb]);
+      });
     }
   }
 }
 
 template <int F, int K, int RB, int NW, int MINB, int PD>
-__global__ void __launch_bounds__(64 * NW, MINB) k_pair_fwd_split(PairFwdArgs a) {
+__global__ void __launch_bounds__(64 * NW, MINB) k_pair_fwd(PairFwdArgs a) {
   constexpr int TILE = 16 * RB;
   const int64_t P = *a.n_pairs <= a.max_pairs ? *a.n_pairs : 0;   // no pair list after an overflow
   const int64_t tile = xcd_block_of((P + TILE - 1) / TILE);
@@ -386,136 +348,18 @@ __global__ void __launch_bounds__(64 * NW, MINB) k_pair_fwd_split(PairFwdArgs a)
     if constexpr (RB == 1)
       read_ahead((P + TILE - 1) / TILE, [&](int part, int parts) {
         constexpr int KP = (K + 31) / 32 * 32;
-        read_range(a.sW0, 6 * F * KP, part, parts);
+        read_range(a.W0, 9 * F * KP, part, parts);
         for (int l = 0; l < a.L; ++l) {
-          read_range(a.sWa[l], 2 * F * KP, part, parts);
-          read_range(a.sWb[l], 4 * F * F, part, parts);
-          read_range(a.sWc[l], 12 * F * F, part, parts);
+          read_range(a.Wa[l], 3 * F * KP, part, parts);
+          read_range(a.Wb[l], 6 * F * F, part, parts);
+          read_range(a.Wc[l], 18 * F * F, part, parts);
         }
       });
     return;
   }
   const int64_t p0 = tile * TILE;
   __shared__ __attribute__((aligned(16))) char smem[sizeof(PairFwdLds<F, K, RB>)];
-  pair_fwd_tile_split<F, K, RB, NW, PD>(a, p0, (int)((P - p0) < TILE ? (P - p0) : TILE), smem);
-}
-
-// One LDS buffer holds the tile's current activation, silu(z1) and then silu(z2); each product
-// keeps its result in registers until every wave has finished reading the buffer.
-template <int F, int K, int RB, int NW>
-__device__ __forceinline__ void pair_fwd_tile(const PairFwdArgs &a, int64_t p0, int nvalid) {
-  constexpr int TILE = 16 * RB;
-  constexpr int LE = K + kPad, L1 = F + kPad, L2 = 2 * F + kPad;
-  __shared__ __attribute__((aligned(16))) float sE[TILE * LE];
-  __shared__ __attribute__((aligned(16))) float sA[TILE * L2];
-  __shared__ double sD[TILE], sPhi[TILE];
-  const int tid = threadIdx.x, wave = tid >> 6;
-
-  if (tid < TILE) {
-    double d = a.r_c, ph = 0.0;
-    if (tid < nvalid) {
-      const int64_t p = p0 + tid;
-      const int64_t i = a.pairs[p], j = a.pairs[a.max_pairs + p];
-      const PairGeo g = pair_geometry(a.pos, i, j, a.lat, a.r_c);
-      d = g.d;
-      ph = g.phi;
-      a.geo[4 * p + 0] = (float)g.u[0];
-      a.geo[4 * p + 1] = (float)g.u[1];
-      a.geo[4 * p + 2] = (float)g.u[2];
-      a.geo[4 * p + 3] = (float)g.d;
-      a.phi[p] = (float)g.phi;
-    }
-    sD[tid] = exp(-a.alpha * (d - a.r_lo));   // the basis argument u, once per pair
-    sPhi[tid] = ph;
-  }
-  __syncthreads();
-  for (int t = tid; t < TILE * K; t += 64 * NW) {
-    const int row = t / K, k = t % K;
-    const double u = sD[row];
-    const double x = u - a.mu[k];
-    sE[row * LE + k] = (float)(sPhi[row] * exp(-a.beta[k] * x * x));
-  }
-  __syncthreads();
-
-  // embedding map f0 = W0 e + b0  (3F outputs; wave covers 3F/NW columns)
-  {
-    constexpr int NB = 3 * F / (16 * NW);
-    floatx4 acc[RB][NB];
-    zero_acc_rb<RB, NB>(acc);
-    const int col0 = wave * (3 * F / NW);
-    float br[NB];
-    load_cols<NB>(a.b0, col0, br);
-    wave_mm_rb<RB, NB>(sE, LE, K, a.W0, col0, acc);
-    for_acc_rc(acc, col0, [&](int, int cb, int, int row, int col, float v) {
-      if (row < nvalid) a.f0[(p0 + row) * 3 * F + col] = v + br[cb];
-    });
-  }
-  for (int l = 0; l < a.L; ++l) {
-    {  // z1 = Wa e + ba
-      constexpr int NB = F / (16 * NW);
-      floatx4 acc[RB][NB];
-      zero_acc_rb<RB, NB>(acc);
-      const int col0 = wave * (F / NW);
-      float br[NB];
-      load_cols<NB>(a.ba[l], col0, br);
-      wave_mm_rb<RB, NB>(sE, LE, K, a.Wa[l], col0, acc);
-      __syncthreads();   // the previous layer's last product has finished reading sA
-      for_acc_rc(acc, col0, [&](int rb, int cb, int t, int row, int col, float v) {
-        // silu'(z1) is all the reverse pass needs of z1, so that is what is stored
-        float g;
-        sA[row * L1 + col] = fast_silu_and_grad(v + br[cb], g);
-        acc[rb][cb][t] = g;
-      });
-      store_acc_blocked<RB, NB>(a.z1[l], F, p0, nvalid, col0, acc);
-    }
-    __syncthreads();
-    {  // z2 = Wb silu(z1) + bb
-      constexpr int NB = 2 * F / (16 * NW);
-      floatx4 acc[RB][NB];
-      zero_acc_rb<RB, NB>(acc);
-      const int col0 = wave * (2 * F / NW);
-      float br[NB];
-      load_cols<NB>(a.bb[l], col0, br);
-      wave_mm_rb<RB, NB>(sA, L1, F, a.Wb[l], col0, acc);
-      __syncthreads();
-      for_acc_rc(acc, col0, [&](int rb, int cb, int t, int row, int col, float v) {
-        float g;
-        sA[row * L2 + col] = fast_silu_and_grad(v + br[cb], g);
-        acc[rb][cb][t] = g;   // stores silu'(z2)
-      });
-      store_acc_blocked<RB, NB>(a.z2[l], 2 * F, p0, nvalid, col0, acc);
-    }
-    __syncthreads();
-    {  // z3 = Wc silu(z2) + bc, h = phi silu(z3)
-      constexpr int NB = 3 * F / (16 * NW);
-      floatx4 acc[RB][NB];
-      zero_acc_rb<RB, NB>(acc);
-      const int col0 = wave * (3 * F / NW);
-      float br[NB];
-      load_cols<NB>(a.bc[l], col0, br);
-      wave_mm_rb<RB, NB>(sA, L2, 2 * F, a.Wc[l], col0, acc);
-      // h is stored only when given: its consumers may instead form it from z3 and phi,
-      // with this same expression
-      float *z3 = a.z3[l], *h = a.h[l];
-      for_acc_rc(acc, col0, [&](int, int cb, int, int row, int col, float v) {
-        const float z = v + br[cb];
-        if (row < nvalid) {
-          z3[(p0 + row) * 3 * F + col] = z;
-          if (h) h[(p0 + row) * 3 * F + col] = (float)sPhi[row] * fast_silu(z);
-        }
-      });
-    }
-  }
-}
-
-template <int F, int K, int RB, int NW, int MINB>
-__global__ void __launch_bounds__(64 * NW, MINB) k_pair_fwd(PairFwdArgs a) {
-  constexpr int TILE = 16 * RB;
-  const int64_t P = *a.n_pairs <= a.max_pairs ? *a.n_pairs : 0;   // no pair list after an overflow
-  const int64_t tile = xcd_block_of((P + TILE - 1) / TILE);
-  if (tile < 0) return;
-  const int64_t p0 = tile * TILE;
-  pair_fwd_tile<F, K, RB, NW>(a, p0, (int)((P - p0) < TILE ? (P - p0) : TILE));
+  pair_fwd_tile<F, K, RB, NW, PD>(a, p0, (int)((P - p0) < TILE ? (P - p0) : TILE), smem);
 }
 
 // ============================================================================ reverse-sweep prologues
@@ -580,63 +424,16 @@ __device__ __forceinline__ void ld_row(const TZ *p, float (&o)[V]) {
   }
 }
 
-// The largest of non-negative integers over the 64 lanes of a wave, wave-uniform.
-__device__ __forceinline__ int wave_max_i(int v) {
-  auto step = [&](int o) { v = o > v ? o : v; };
-  step(__builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false));
-  step(__builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false));
-  step(__builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false));
-  step(__builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false));
-  const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
-  const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-  const int a = r0 > r1 ? r0 : r1, b = r2 > r3 ? r2 : r3;
-  return a > b ? a : b;
-}
-
-// Stores this wave's adjoint row (three parts of F channels, V per lane) to the tile: as it is, or,
-// for the split kernels (TL = _Float16), as hi and lo halves scaled by the power of two that brings
-// the row's largest entry into [2^14, 2^15); returns the factor that takes the scale off again.
-// Rows below 2^-112 keep the scale of 2^-112; a row with an infinity or NaN stays non-finite.
-template <class TL, int F, int V>
-__device__ __forceinline__ float st_adjoint_row(TL *row, int lo, int f, const float (&o)[3][V]) {
-  if constexpr (std::is_same<TL, _Float16>::value) {
-    int top = 0;
+// Stores this wave's adjoint row (three parts of F channels, V per lane) to the tile: rounded to BF16,
+// or, for the FP32 kernels (SPLIT), as the three BF16 parts of each number, `plane` elements apart.
+template <bool SPLIT, int F, int V>
+__device__ __forceinline__ void st_adjoint_row(__bf16 *row, int plane, int f, const float (&o)[3][V]) {
 #pragma unroll
-    for (int pt = 0; pt < 3; ++pt)
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const int b = __builtin_bit_cast(int, o[pt][v]) & 0x7fffffff;
-        top = b > top ? b : top;
-      }
-    int e = wave_max_i(top) >> 23;
-    e = e < 15 ? 15 : e;
-    const float sc = __builtin_bit_cast(float, (268 - e) << 23);
-#pragma unroll
-    for (int pt = 0; pt < 3; ++pt) {
-      _Float16 h[V], l[V];
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const float x = o[pt][v] * sc;
-        h[v] = (_Float16)x;
-        l[v] = (_Float16)(x - (float)h[v]);
-      }
-      if constexpr (V == 2) {   // one 4-byte access each (even channel offsets)
-        typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-        *reinterpret_cast<half2v *>(row + pt * F + f) = half2v{h[0], h[1]};
-        *reinterpret_cast<half2v *>(row + lo + pt * F + f) = half2v{l[0], l[1]};
-      } else {
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          row[pt * F + f + v] = h[v];
-          row[lo + pt * F + f + v] = l[v];
-        }
-      }
-    }
-    return __builtin_bit_cast(float, (e - 14) << 23);
-  } else {
-#pragma unroll
-    for (int pt = 0; pt < 3; ++pt) st_row<TL, V>(row + pt * F + f, o[pt]);
-    return 1.f;
+  for (int pt = 0; pt < 3; ++pt) {
+    if constexpr (SPLIT)
+      st_split<V>(row + pt * F + f, plane, o[pt]);
+    else
+      st_row<__bf16, V>(row + pt * F + f, o[pt]);
   }
 }
 
@@ -688,11 +485,11 @@ struct EmbedRowJ {
 
 // dE/df0 = (da, db, dc) for both directions of the pair -> lds[row][0..3F); returns the pair's
 // dE/dphi and dE/dvhat (embedding part) through the per-row LDS arrays.
-template <int F, int R, class TL, int NW = 4, int PF = 2, class TF = float>
+template <int F, int R, bool SPLIT, int NW = 4, int PF = 2, class TF = float>
 __device__ __forceinline__ void embed_adjoint_rows(const BwdGather &bg, const int32_t *pairs, int64_t max_pairs,
                                                    int64_t p0, int nvalid, const float (*sU)[3], const float *sPhi,
-                                                   TL *lds, int ld, float *sDphi, float (*sDv)[3],
-                                                   int lo = 0, float *sInv = nullptr) {
+                                                   __bf16 *lds, int ld, float *sDphi, float (*sDv)[3],
+                                                   int plane = 0) {
 #pragma clang fp contract(on)   // fused multiply-adds per expression only, so every tile shape rounds alike
   constexpr int V = F / 64, rows = R / NW;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
@@ -763,13 +560,12 @@ __device__ __forceinline__ void embed_adjoint_rows(const BwdGather &bg, const in
       av1 += ph * (b * (Zij * xi[2] - Zji * xj[2]) + c * (Zij * gsi[1] + Zji * gsj[1]));
       av2 += ph * (b * (Zij * xi[3] - Zji * xj[3]) + c * (Zij * gsi[2] + Zji * gsj[2]));
     }
-    const float inv = st_adjoint_row<TL, F, V>(lds + row * ld, lo, f, o);
+    st_adjoint_row<SPLIT, F, V>(lds + row * ld, plane, f, o);
     aphi = wave_sum(valid ? aphi : 0.f);
     av0 = wave_sum(valid ? av0 : 0.f);
     av1 = wave_sum(valid ? av1 : 0.f);
     av2 = wave_sum(valid ? av2 : 0.f);
     if (lane == 0) {
-      if (sInv) sInv[row] = inv;
       sDphi[row] = aphi;
       sDv[row][0] = av0;
       sDv[row][1] = av1;
@@ -800,11 +596,11 @@ struct FilterRowJ {
 // Layer l: dh = <part(Y_j), dM_i> + <part(Y_i), dM_j> per channel; then
 // lds[row][c] = dh phi silu'(z3) and dE/dphi += sum_c dh silu(z3).  The atom rows Y and dM are
 // read as TY (FP32, or the BF16 copies of the BF16 path).
-template <int F, int R, class TL, class TZ, int NW = 4, int PF = 2, class TY = float>
+template <int F, int R, bool SPLIT, class TZ, int NW = 4, int PF = 2, class TY = float>
 __device__ __forceinline__ void filter_adjoint_rows(const TY *Y, const TY *dM, const TZ *z3,
                                                     const int32_t *pairs, int64_t max_pairs, int64_t p0, int nvalid,
-                                                    const float *sPhi, TL *lds, int ld, float *sDphi, int lo = 0,
-                                                    float *sInv = nullptr) {
+                                                    const float *sPhi, __bf16 *lds, int ld, float *sDphi,
+                                                    int plane = 0) {
 #pragma clang fp contract(on)   // fused multiply-adds per expression only, so every tile shape rounds alike
   constexpr int V = F / 64, rows = R / NW;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
@@ -857,12 +653,9 @@ __device__ __forceinline__ void filter_adjoint_rows(const TY *Y, const TY *dM, c
         o[pt][v] = valid ? dh[pt][v] * ph * fast_silu_grad(cur.z[pt][v]) : 0.f;
         part += dh[pt][v] * fast_silu(cur.z[pt][v]);
       }
-    const float inv = st_adjoint_row<TL, F, V>(lds + row * ld, lo, f, o);
+    st_adjoint_row<SPLIT, F, V>(lds + row * ld, plane, f, o);
     part = wave_sum(valid ? part : 0.f);
-    if (lane == 0) {
-      if (sInv) sInv[row] = inv;
-      sDphi[row] += part;
-    }
+    if (lane == 0) sDphi[row] += part;
   }
 }
 
@@ -945,141 +738,32 @@ __device__ __forceinline__ void geometry_adjoint_tile(const PairGeo *sGeo, const
 
 // ============================================================================ reverse
 // One LDS buffer holds the tile's current adjoint: dE/df0, then per layer dz3, dz2, dz1, and
-// finally dE/de.  Each product keeps its result in registers until every wave has finished
-// reading the buffer, so the tile needs ~50 KB of LDS and two blocks share a CU.  Of z1 and z2
+// finally dE/de, in three BF16 parts.  Each product keeps its result in registers until every wave has
+// finished reading the buffer, so 32 pairs need 78 KB at F = 128 and two blocks share a CU.  Of z1 and z2
 // the reverse pass needs only silu'(z1) and silu'(z2), which the forward pass stores in their
 // place (it has the sigmoid at hand), so no transcendental is evaluated for them here.  They
-// are loaded, not recomputed: recomputing z1 = Wa e + ba from the basis (8 kFLOP per pair and
-// layer) made the reverse launch 0.47 ms slower on a 100,000-atom box (19.45 against 18.98 ms)
+// are loaded, not recomputed: with the products on FP32 instructions, recomputing z1 = Wa e + ba from
+// the basis (8 kFLOP per pair and layer) made the reverse launch 0.47 ms slower on a 100,000-atom box (19.45 against 18.98 ms)
 // and the forward, which then skips the store, 0.21 ms faster; recomputing f0 as well, 0.5 ms
 // slower still.
 
-// PF: how much of the next row the prologues prefetch (by the register budget of the caller's
-// launch bound; 2 = pair row and atom rows, 1 = pair row, 0 = none)
-template <int F, int K, int RB, int NW, int PF>
-__device__ __forceinline__ void pair_bwd_tile(const PairBwdArgs &a, int64_t p0, int nvalid) {
-  constexpr int TILE = 16 * RB;
-  constexpr int L3 = 3 * F + kPad, L2 = 2 * F + kPad, L1 = F + kPad, LE = K + kPad;
-  __shared__ __attribute__((aligned(16))) float sG[TILE * L3];
-  __shared__ float sPhi[TILE], sDphi[TILE], sU[TILE][3], sDv[TILE][3];
-  __shared__ PairGeo sGeo[TILE];   // FP64 geometry for the final dE/dv, kept out of registers
-  const int tid = threadIdx.x, wave = tid >> 6;
-  // dE/de is split into (16-row block, 16-column block) pieces dealt round-robin to the waves
-  constexpr int KB = K / 16, NDE = (RB * KB + NW - 1) / NW;
-
-  if (tid < TILE) {
-    PairGeo g{};
-    float ph = 0.f;
-    if (tid < nvalid) {
-      const int64_t p = p0 + tid;
-      g = pair_geometry(a.pos, a.pairs[p], a.pairs[a.max_pairs + p], a.lat, a.r_c);
-      ph = (float)g.phi;
-    }
-    sPhi[tid] = ph;
-    sU[tid][0] = (float)g.u[0];
-    sU[tid][1] = (float)g.u[1];
-    sU[tid][2] = (float)g.u[2];
-    sGeo[tid] = g;
-  }
-  __syncthreads();
-  // embedding adjoint: dE/df0 -> sG, dE/dphi and dE/dvhat per pair
-  embed_adjoint_rows<F, TILE, float, NW, PF>(a.g, a.pairs, a.max_pairs, p0, nvalid, sU, sPhi, sG, L3, sDphi, sDv);
-  __syncthreads();
-  floatx4 de[NDE][1][1];
-  auto de_product = [&](const float *act, int ld, int Kin, const float *Bt) {
-#pragma unroll
-    for (int n = 0; n < NDE; ++n) {
-      const int c = wave + NW * n;
-      if (c < RB * KB) wave_mm_rows<1, 1>(act + (c / KB) * 16 * ld, ld, 16 * ld, Kin, Bt, (c % KB) * 16, de[n]);
-    }
-  };
-#pragma unroll
-  for (int n = 0; n < NDE; ++n) zero_acc_rb<1, 1>(de[n]);
-  de_product(sG, L3, 3 * F, a.W0T);
-  __syncthreads();
-
-  for (int l = 0; l < a.L; ++l) {
-    const float *z1 = a.z1[l], *z2 = a.z2[l];
-    filter_adjoint_rows<F, TILE, float, float, NW, PF>(a.g.Y[l], a.g.dM[l], a.z3[l], a.pairs, a.max_pairs, p0, nvalid, sPhi, sG, L3,
-                                  sDphi);
-    __syncthreads();
-    {  // dz2 = (dz3 Wc) silu'(z2)
-      constexpr int NB = 2 * F / (16 * NW);
-      floatx4 acc[RB][NB];
-      zero_acc_rb<RB, NB>(acc);
-      const int col0 = wave * (2 * F / NW);
-      float zp[RB][NB][4];
-      load_acc_blocked<RB, NB>(z2, 2 * F, p0, nvalid, col0, zp);
-      wave_mm_rb<RB, NB>(sG, L3, 3 * F, a.WcT[l], col0, acc);
-      __syncthreads();
-      for_acc_rc(acc, col0, [&](int rb, int cb, int t, int row, int col, float v) {
-        sG[row * L2 + col] = row < nvalid ? v * zp[rb][cb][t] : 0.f;   // zp = silu'(z2)
-      });
-    }
-    __syncthreads();
-    {  // dz1 = (dz2 Wb) silu'(z1)
-      constexpr int NB = F / (16 * NW);
-      floatx4 acc[RB][NB];
-      zero_acc_rb<RB, NB>(acc);
-      const int col0 = wave * (F / NW);
-      float zp[RB][NB][4];
-      load_acc_blocked<RB, NB>(z1, F, p0, nvalid, col0, zp);
-      wave_mm_rb<RB, NB>(sG, L2, 2 * F, a.WbT[l], col0, acc);
-      __syncthreads();
-      for_acc_rc(acc, col0, [&](int rb, int cb, int t, int row, int col, float v) {
-        sG[row * L1 + col] = row < nvalid ? v * zp[rb][cb][t] : 0.f;   // zp = silu'(z1)
-      });
-    }
-    __syncthreads();
-    de_product(sG, L1, F, a.WaT[l]);   // de += dz1 Wa
-    __syncthreads();
-  }
-
-  float *sDE = sG;   // [TILE][K+4]
-#pragma unroll
-  for (int n = 0; n < NDE; ++n) {
-    const int c = wave + NW * n;
-    if (c < RB * KB)
-      for_acc_rc(de[n], (c % KB) * 16, [&](int, int, int, int row, int col, float v) {
-        sDE[((c / KB) * 16 + row) * LE + col] = v;
-      });
-  }
-  __syncthreads();
-  geometry_adjoint_tile<K, TILE, 64 * NW>(sGeo, sDE, LE, sDphi, sDv, nvalid, a.alpha, a.r_lo, a.mu, a.beta,
-                                          a.gpair + 3 * p0);
-}
-
-template <int F, int K, int RB, int NW, int MINB>
-__global__ void __launch_bounds__(64 * NW, MINB) k_pair_bwd(PairBwdArgs a) {
-  constexpr int TILE = 16 * RB;
-  // how much of the next row the prologues prefetch, by the register budget (MINB waves per SIMD)
-  constexpr int PF = MINB <= 2 ? 2 : (MINB == 3 ? 1 : 0);
-  const int64_t P = *a.n_pairs <= a.max_pairs ? *a.n_pairs : 0;   // no pair list after an overflow
-  const int64_t tile = xcd_block_of((P + TILE - 1) / TILE);
-  if (tile < 0) return;
-  const int64_t p0 = tile * TILE;
-  pair_bwd_tile<F, K, RB, NW, PF>(a, p0, (int)((P - p0) < TILE ? (P - p0) : TILE));
-}
-
-// The reverse tile on split operands, the counterpart of pair_fwd_tile_split.  A pair's row of
-// adjoints (dE/df0, then each layer's dz3) is scaled by its own largest entry as the prologue
-// writes it, the factor kept in sInv; dz2 and dz1 keep that scale, less the bound of their growth.
-// dE/de is summed in FP32 over the embedding and the layers, each product's scales taken off first.
 template <int F, int RB>
 struct PairBwdLds {
   static constexpr int TILE = 16 * RB;
-  __attribute__((aligned(16))) _Float16 G[2 * TILE * (3 * F + kPadH)];
-  float phi[TILE], dphi[TILE], u[TILE][3], dv[TILE][3], inv[TILE];
+  __attribute__((aligned(16))) __bf16 G[3 * TILE * (3 * F + kPadH)];
+  float phi[TILE], dphi[TILE], u[TILE][3], dv[TILE][3];
   PairGeo geo[TILE];   // FP64 geometry for the final dE/dv, kept out of registers
 };
+// PF: how much of the next row the prologues prefetch (by the register budget of the caller's
+// launch bound; 2 = pair row and atom rows, 1 = pair row, 0 = none)
 template <int F, int K, int RB, int NW, int PF, int PD = 1>
-__device__ __forceinline__ void pair_bwd_tile_split(const PairBwdArgs &a, int64_t p0, int nvalid, char *smem) {
+__device__ __forceinline__ void pair_bwd_tile(const PairBwdArgs &a, int64_t p0, int nvalid, char *smem) {
   constexpr int TILE = 16 * RB;
   constexpr int L3 = 3 * F + kPadH, L2 = 2 * F + kPadH, L1 = F + kPadH, LE = K + kPad;
   using Lds = PairBwdLds<F, RB>;
   Lds &lds = *reinterpret_cast<Lds *>(smem);
-  _Float16 *sG = lds.G;
-  float *sPhi = lds.phi, *sDphi = lds.dphi, *sInv = lds.inv;
+  __bf16 *sG = lds.G;
+  float *sPhi = lds.phi, *sDphi = lds.dphi;
   float(*sU)[3] = lds.u, (*sDv)[3] = lds.dv;
   PairGeo *sGeo = lds.geo;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -1101,65 +785,65 @@ __device__ __forceinline__ void pair_bwd_tile_split(const PairBwdArgs &a, int64_
     sGeo[tid] = g;
   }
   __syncthreads();
-  embed_adjoint_rows<F, TILE, _Float16, NW, PF>(a.g, a.pairs, a.max_pairs, p0, nvalid, sU, sPhi, sG, L3, sDphi, sDv,
-                                                TILE * L3, sInv);
+  // embedding adjoint: dE/df0 -> sG, dE/dphi and dE/dvhat per pair
+  embed_adjoint_rows<F, TILE, true, NW, PF>(a.g, a.pairs, a.max_pairs, p0, nvalid, sU, sPhi, sG, L3, sDphi, sDv,
+                                            TILE * L3);
   __syncthreads();
-  floatx4 de[NDE];
+  floatx4 de[NDE][1][1];
 #pragma unroll
-  for (int n = 0; n < NDE; ++n) de[n] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto de_product = [&](auto kc, int ld, const _Float16 *Bt, float j) {
+  for (int n = 0; n < NDE; ++n) zero_acc_rb<1, 1>(de[n]);
+  auto de_product = [&](auto kc, int ld, const __bf16 *Bt) {
 #pragma unroll
     for (int n = 0; n < NDE; ++n) {
       const int c = wave + NW * n;
       if (c < RB * KB) {
-        floatx4 acc[1][1];
-        zero_acc_rb<1, 1>(acc);
-        wave_mm_split<1, 1, decltype(kc)::value, PD>(sG + (c / KB) * 16 * ld, TILE * ld, ld, Bt, c % KB, acc);
-        de[n] = fma4(acc[0][0], sInv[(c / KB) * 16 + (lane & 15)] * j, de[n]);
+        SplitWeights<1, decltype(kc)::value, PD> w(Bt, c % KB);
+        wave_mm_split(sG + (c / KB) * 16 * ld, TILE * ld, ld, w, de[n]);
       }
     }
   };
-  de_product(std::integral_constant<int, 3 * F / 32>{}, L3, a.sW0T, a.j0);
+  de_product(std::integral_constant<int, 3 * F / 32>{}, L3, a.W0T);
   __syncthreads();
 
-  // a product's accumulator, less its growth, times silu' (zp) to sG; rows past nvalid are zero
-  auto gate = [&](auto cols, auto &acc, const auto &zp, float f, int ld) {
+  // a product's accumulator times silu' (zp) to sG; rows past nvalid are zero
+  auto gate = [&](auto cols, auto &acc, const auto &zp, int ld) {
     using C = decltype(cols);
     for_acc_t(acc, C::col0(wave), [&](int rb, int cb, int row, int col, floatx4 &v) {
       floatx4 x = floatx4{0.f, 0.f, 0.f, 0.f};
-      if (row < nvalid) x = v * f * zp[rb][cb];
+      if (row < nvalid) x = v * zp[rb][cb];
       st4_split(sG + row * ld + col, TILE * ld, x);
     });
   };
+  using C1 = WaveCols<F, NW>;
+  using C2 = WaveCols<2 * F, NW>;
   for (int l = 0; l < a.L; ++l) {
-    filter_adjoint_rows<F, TILE, _Float16, float, NW, PF>(a.g.Y[l], a.g.dM[l], a.z3[l], a.pairs, a.max_pairs, p0,
-                                                          nvalid, sPhi, sG, L3, sDphi, TILE * L3, sInv);
+    filter_adjoint_rows<F, TILE, true, float, NW, PF>(a.g.Y[l], a.g.dM[l], a.z3[l], a.pairs, a.max_pairs, p0, nvalid,
+                                                      sPhi, sG, L3, sDphi, TILE * L3);
+    // each product's first weights before the barrier and stores ahead of it
+    SplitWeights<C2::NB, 3 * F / 32, PD> wc(a.WcT[l], C2::cb0(C2::on(wave) ? wave : 0));
     __syncthreads();
-    {  // dz2 = (dz3 Wc) silu'(z2)
-      using C = WaveCols<2 * F, NW>;
-      floatx4 acc[RB][C::NB], zp[RB][C::NB];
-      if (C::on(wave)) {
-        zero_acc_rb<RB, C::NB>(acc);
-        load_acc_blocks_t<RB, C::NB>(a.z2[l], 2 * F, p0, nvalid, C::cb0(wave), zp);
-        wave_mm_split<RB, C::NB, 3 * F / 32, PD>(sG, TILE * L3, L3, a.sWcT[l], C::cb0(wave), acc);
-      }
-      __syncthreads();
-      if (C::on(wave)) gate(C(), acc, zp, a.f2[l], L2);
+    // dz2 = (dz3 Wc) silu'(z2)
+    floatx4 acc2[RB][C2::NB], zp2[RB][C2::NB];
+    if (C2::on(wave)) {
+      zero_acc_rb<RB, C2::NB>(acc2);
+      load_acc_blocks_t<RB, C2::NB>(a.z2[l], 2 * F, p0, nvalid, C2::cb0(wave), zp2);
+      wave_mm_split(sG, TILE * L3, L3, wc, acc2);
+    }
+    SplitWeights<C1::NB, 2 * F / 32, PD> wb(a.WbT[l], C1::cb0(C1::on(wave) ? wave : 0));
+    __syncthreads();
+    if (C2::on(wave)) gate(C2(), acc2, zp2, L2);
+    __syncthreads();
+    // dz1 = (dz2 Wb) silu'(z1)
+    floatx4 acc1[RB][C1::NB], zp1[RB][C1::NB];
+    if (C1::on(wave)) {
+      zero_acc_rb<RB, C1::NB>(acc1);
+      load_acc_blocks_t<RB, C1::NB>(a.z1[l], F, p0, nvalid, C1::cb0(wave), zp1);
+      wave_mm_split(sG, TILE * L2, L2, wb, acc1);
     }
     __syncthreads();
-    {  // dz1 = (dz2 Wb) silu'(z1)
-      using C = WaveCols<F, NW>;
-      floatx4 acc[RB][C::NB], zp[RB][C::NB];
-      if (C::on(wave)) {
-        zero_acc_rb<RB, C::NB>(acc);
-        load_acc_blocks_t<RB, C::NB>(a.z1[l], F, p0, nvalid, C::cb0(wave), zp);
-        wave_mm_split<RB, C::NB, 2 * F / 32, PD>(sG, TILE * L2, L2, a.sWbT[l], C::cb0(wave), acc);
-      }
-      __syncthreads();
-      if (C::on(wave)) gate(C(), acc, zp, a.f1[l], L1);
-    }
+    if (C1::on(wave)) gate(C1(), acc1, zp1, L1);
     __syncthreads();
-    de_product(std::integral_constant<int, F / 32>{}, L1, a.sWaT[l], a.ja[l]);   // de += dz1 Wa
+    de_product(std::integral_constant<int, F / 32>{}, L1, a.WaT[l]);   // de += dz1 Wa
     __syncthreads();
   }
 
@@ -1167,7 +851,7 @@ __device__ __forceinline__ void pair_bwd_tile_split(const PairBwdArgs &a, int64_
 #pragma unroll
   for (int n = 0; n < NDE; ++n) {
     const int c = wave + NW * n;
-    if (c < RB * KB) st4(sDE + ((c / KB) * 16 + (lane & 15)) * LE + (c % KB) * 16 + 4 * (lane >> 4), de[n]);
+    if (c < RB * KB) st4(sDE + ((c / KB) * 16 + (lane & 15)) * LE + (c % KB) * 16 + 4 * (lane >> 4), de[n][0][0]);
   }
   __syncthreads();
   geometry_adjoint_tile<K, TILE, 64 * NW>(sGeo, sDE, LE, sDphi, sDv, nvalid, a.alpha, a.r_lo, a.mu, a.beta,
@@ -1175,7 +859,7 @@ __device__ __forceinline__ void pair_bwd_tile_split(const PairBwdArgs &a, int64_
 }
 
 template <int F, int K, int RB, int NW, int MINB, int PD>
-__global__ void __launch_bounds__(64 * NW, MINB) k_pair_bwd_split(PairBwdArgs a) {
+__global__ void __launch_bounds__(64 * NW, MINB) k_pair_bwd(PairBwdArgs a) {
   constexpr int TILE = 16 * RB;
   // how much of the next row the prologues prefetch, by the register budget (MINB waves per SIMD)
   constexpr int PF = MINB <= 2 ? 2 : (MINB == 3 ? 1 : 0);
@@ -1184,18 +868,18 @@ __global__ void __launch_bounds__(64 * NW, MINB) k_pair_bwd_split(PairBwdArgs a)
   if (tile < 0) {
     if constexpr (RB == 1)
       read_ahead((P + TILE - 1) / TILE, [&](int part, int parts) {
-        read_range(a.sW0T, 6 * F * K, part, parts);
+        read_range(a.W0T, 9 * F * K, part, parts);
         for (int l = 0; l < a.L; ++l) {
-          read_range(a.sWcT[l], 12 * F * F, part, parts);
-          read_range(a.sWbT[l], 4 * F * F, part, parts);
-          read_range(a.sWaT[l], 2 * F * K, part, parts);
+          read_range(a.WcT[l], 18 * F * F, part, parts);
+          read_range(a.WbT[l], 6 * F * F, part, parts);
+          read_range(a.WaT[l], 3 * F * K, part, parts);
         }
       });
     return;
   }
   const int64_t p0 = tile * TILE;
   __shared__ __attribute__((aligned(16))) char smem[sizeof(PairBwdLds<F, RB>)];
-  pair_bwd_tile_split<F, K, RB, NW, PF, PD>(a, p0, (int)((P - p0) < TILE ? (P - p0) : TILE), smem);
+  pair_bwd_tile<F, K, RB, NW, PF, PD>(a, p0, (int)((P - p0) < TILE ? (P - p0) : TILE), smem);
 }
 
 // ============================================================================ BF16 variant
@@ -1207,7 +891,7 @@ __global__ void __launch_bounds__(64 * NW, MINB) k_pair_bwd_split(PairBwdArgs a)
 
 // acc[rb][cb] += act[16*RB x Kin] (LDS bf16, row stride ld) * Bt^T (Bt [ncol][Kin] bf16 in global
 // memory); with TR the operands of each instruction are swapped and the accumulator holds the
-// block transposed, as with wave_mm_t (visit it with for_acc_t).
+// block transposed (visit it with for_acc_t).
 template <int RB, int NB, bool TR = false>
 __device__ __forceinline__ void wave_mm_bf16(const __bf16 *act, int ld, int Kin, const __bf16 *__restrict__ Bt,
                                              int col0, floatx4 (&acc)[RB][NB]) {
@@ -1381,7 +1065,7 @@ __device__ __forceinline__ void pair_bwd_tile_bf16(const PairBwdArgsB &a, int64_
     sU[tid][2] = (float)g.u[2];
   }
   __syncthreads();
-  embed_adjoint_rows<F, TILE, __bf16, NW, PF, __bf16>(a.g, a.pairs, a.max_pairs, p0, nvalid, sU, sPhi, sG, L3, sDphi,
+  embed_adjoint_rows<F, TILE, false, NW, PF, __bf16>(a.g, a.pairs, a.max_pairs, p0, nvalid, sU, sPhi, sG, L3, sDphi,
                                                    sDv);
   __syncthreads();
   // de += act * Bt^T for this wave's 16 columns of dE/de (waves < NWDE), through sDE
@@ -1404,7 +1088,7 @@ __device__ __forceinline__ void pair_bwd_tile_bf16(const PairBwdArgsB &a, int64_
   __syncthreads();
   for (int l = 0; l < a.L; ++l) {
     const __bf16 *z1 = a.z1[l], *z2 = a.z2[l];
-    filter_adjoint_rows<F, TILE, __bf16, __bf16, NW, PF, __bf16>(a.Y16[l], a.dM16[l], a.z3[l], a.pairs, a.max_pairs, p0,
+    filter_adjoint_rows<F, TILE, false, __bf16, NW, PF, __bf16>(a.Y16[l], a.dM16[l], a.z3[l], a.pairs, a.max_pairs, p0,
                                                             nvalid, sPhi, sG, L3,
                                    sDphi);
     __syncthreads();

@@ -268,13 +268,6 @@ __device__ __forceinline__ void st_split8(__bf16 *p, int plane, const float (&x)
     *reinterpret_cast<uint4 *>(p + n * plane) = o[n];
   }
 }
-struct Frag3 {
-  bf16x8 h, m, l;
-};
-__device__ __forceinline__ Frag3 ld_frag3(const __bf16 *p, int plane) {
-  return Frag3{*reinterpret_cast<const bf16x8 *>(p), *reinterpret_cast<const bf16x8 *>(p + plane),
-               *reinterpret_cast<const bf16x8 *>(p + 2 * plane)};
-}
 // c += a b: the five smaller products are summed by themselves, so that the sum's rounding is that of one
 // product per chunk.  Measured against 64 bits over the gradient of 12 models (relative norm): F = 128,
 // three layers 2.7e-7 (FP32 instructions 3.9e-7; one sum 3.1e-7), one layer 3.5e-7 (4.0e-7; 4.3e-7),
