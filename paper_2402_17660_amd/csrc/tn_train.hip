@@ -238,40 +238,16 @@ __global__ void __launch_bounds__(256) k_gemm_dual(DualGemmArgs<S> g) {
 }
 
 // ---------------------------------------------------------------- FP32 products as BF16 products
-// A float is cut into three BF16 numbers of its leading, middle and trailing eight significant bits (by
-// truncation: exact, and BF16 has FP32's exponents, so adjoints of any size need no scale).  A
-// product is the six largest of the nine BF16 products with FP32 accumulation; the other three are
-// 2^-24 of it.  Six v_mfma_f32_16x16x32_bf16 do the work of eight v_mfma_f32_16x16x4_f32 in 96 matrix
-// cycles instead of 256.  An infinity becomes NaN.
+// The products of tn_mfma.h's three BF16 parts: exact operands of any size (BF16 has FP32's exponents, so
+// adjoints need no scale), the six largest of nine BF16 products, FP32 accumulation.  An infinity becomes
+// NaN.
 constexpr int kPadT = 8;   // LDS row padding (elements)
 
-__device__ __forceinline__ float bf16_top(float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u); }
-__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
-  return (__builtin_bit_cast(uint32_t, a) >> 16) | (__builtin_bit_cast(uint32_t, b) & 0xffff0000u);
-}
-// Eight floats to p (hi), p + plane (middle), p + 2 plane (low): 16-byte stores.
-__device__ __forceinline__ void st_split8(__bf16 *p, int plane, const float (&x)[8]) {
-  uint4 o[3];
-  float r[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) r[t] = x[t];
-#pragma unroll
-  for (int n = 0; n < 3; ++n) {
-    o[n].x = bf16_pair(r[0], r[1]);
-    o[n].y = bf16_pair(r[2], r[3]);
-    o[n].z = bf16_pair(r[4], r[5]);
-    o[n].w = bf16_pair(r[6], r[7]);
-    if (n < 2) {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) r[t] -= bf16_top(r[t]);
-    }
-    *reinterpret_cast<uint4 *>(p + n * plane) = o[n];
-  }
-}
 // c += a b: the five smaller products are summed by themselves, so that the sum's rounding is that of one
 // product per chunk.  Measured against 64 bits over the gradient of 12 models (relative norm): F = 128,
-// three layers 2.7e-7 (FP32 instructions 3.9e-7; one sum 3.1e-7), one layer 3.5e-7 (4.0e-7; 4.3e-7),
-// F = 64 3.3e-7 (3.6e-7; 3.6e-7).
+// three layers 3.1e-7, one layer 2.7e-7, F = 64 2.8e-7.  (FP32 instructions 5.6e-7, 4.4e-7, 4.0e-7; parts cut
+// off instead of rounded 3.7e-7, 3.6e-7, 3.5e-7: what is left out then reaches 2^-21 of a product and
+// has its sign.)
 __device__ __forceinline__ void mfma3(const Frag3 &a, const Frag3 &b, floatx4 &c, floatx4 &small) {
   small = mfma_bf16(a.l, b.h, small);
   small = mfma_bf16(a.h, b.l, small);
@@ -349,12 +325,12 @@ __global__ void __launch_bounds__(256, 2) k_gemm_dual_split(DualGemmArgs<float> 
       v[t] = ra[t / 4][t % 4].v;
       d[t] = ra[t / 4][t % 4].d;
     }
-    st_split8(sA + arow * LD + akk, PA, v);
-    st_split8(sA + (BM + arow) * LD + akk, PA, d);
+    st_split<8>(sA + arow * LD + akk, PA, v);
+    st_split<8>(sA + (BM + arow) * LD + akk, PA, d);
 #pragma unroll
     for (int e = 0; e < NB; ++e) {
       const int n = (g.transB ? tid >> 2 : lane) + 64 * e, kk = g.transB ? akk : (tid >> 6) * 8;
-      st_split8(sB + n * LD + kk, PB, rb[e]);
+      st_split<8>(sB + n * LD + kk, PB, rb[e]);
     }
   };
   floatx4 acc[2][BM / 16][NB], low[2][BM / 16][NB];
@@ -662,8 +638,8 @@ __global__ void __launch_bounds__(4 * TO) k_wgrad_split(const Dual<float> *A, Ro
       v[t] = x[t].v;
       d[t] = x[t].d;
     }
-    st_split8(s + c * LD + g, plane, v);
-    st_split8(s + (cols + c) * LD + g, plane, d);
+    st_split<8>(s + c * LD + g, plane, v);
+    st_split<8>(s + (cols + c) * LD + g, plane, d);
   };
   floatx4 acc[AO][2], low[AO][2];
 #pragma unroll
