@@ -239,8 +239,8 @@ __global__ void __launch_bounds__(256) k_gemm_dual(DualGemmArgs<S> g) {
 
 // ---------------------------------------------------------------- FP32 products as BF16 products
 // The products of tn_mfma.h's three BF16 parts: exact operands of any size (BF16 has FP32's exponents, so
-// adjoints need no scale), the six largest of nine BF16 products, FP32 accumulation.  An infinity becomes
-// NaN.
+// adjoints need no scale), the six largest of nine BF16 products, FP32 accumulation.  Of an infinity the
+// remainders are NaN: a sum that comes out NaN is formed again from the operands themselves.
 constexpr int kPadT = 8;   // LDS row padding (elements)
 
 // c += a b: the five smaller products are summed by themselves, so that the sum's rounding is that of one
@@ -373,7 +373,19 @@ __global__ void __launch_bounds__(256, 2) k_gemm_dual_split(DualGemmArgs<float> 
       if (m >= Mrows) continue;
       D v[4], x[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = D(acc[0][a][b][t] + low[0][a][b][t] + bias[t], acc[1][a][b][t] + low[1][a][b][t]);
+      for (int t = 0; t < 4; ++t) {
+        v[t] = D(acc[0][a][b][t] + low[0][a][b][t], acc[1][a][b][t] + low[1][a][b][t]);
+        if (__builtin_expect(isnan(v[t].v) || isnan(v[t].d), 0)) {
+          v[t] = D(0.f, 0.f);
+          for (int64_t k = 0; k < g.K; ++k) {
+            const D x = A[m * g.lda + k];
+            const float w = g.transB ? B[(n + t) * g.ldb + k] : B[k * g.ldb + n + t];
+            v[t].v += x.v * w;
+            v[t].d += x.d * w;
+          }
+        }
+        v[t].v += bias[t];
+      }
       if (g.Z) st_dual4(g.Z + z * g.zoff + m * g.ldz + n, v);
       if (g.act == 1) {
 #pragma unroll
@@ -680,6 +692,16 @@ __global__ void __launch_bounds__(4 * TO) k_wgrad_split(const Dual<float> *A, Ro
     for (int b = 0; b < 2; ++b) {
       const int o = o0 + wo + 16 * a + r16, k = k0 + wk + 16 * b + 4 * q;
       acc[a][b] += low[a][b];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (__builtin_expect(isnan(acc[a][b][t]), 0)) {
+          float s = 0.f;
+          for (int64_t r = rb; r < re; ++r) {
+            const D x = A[row_at(ma, r) + o], y = B[row_at(mb, r) + k + t];
+            s += x.v * y.d + x.d * y.v;
+          }
+          acc[a][b][t] = s;
+        }
       const D v[4] = {D(0.f, acc[a][b][0]), D(0.f, acc[a][b][1]), D(0.f, acc[a][b][2]), D(0.f, acc[a][b][3])};
       st_dual4(P + ((int64_t)blockIdx.z * O + o) * Kc + k, v);
     }
