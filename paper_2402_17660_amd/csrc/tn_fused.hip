@@ -39,16 +39,17 @@ template <class TA>
 struct FusedWs {
   NbrWs nb;
   float *geo, *phi, *f0, *Xr, *T0;
-  TA *nrm0, *xhat0, *rstd0, *n0, *ez1, *ea1, *ez2, *g;
+  TA *nrm0 = nullptr, *xhat0, *rstd0, *n0, *ez1, *ea1, *ez2, *g;
   std::vector<float *> X, nX, Xb, Y, z1, z2, z3, h, M, P, nP, Pb, D, dM;
   std::vector<__bf16 *> Y16, dM16;   // BF16 copies of Y and dM for the gathers (BF16 path)
-  TA *on, *oxhat, *orstd, *q, *oz, *ox, *hx, *eps;
-  float *dX = nullptr, *dD, *dPb, *dY, *dXr, *dT0;
-  // BF16 path: Pb, dD, dY + its gathered sum, and dT0 are read only by the next channel mixing,
-  // which rounds them to BF16, so their producers write them rounded, here (one at a time;
-  // the FP32 buffers Pb, dD and dT0 are then not allocated)
+  TA *on = nullptr, *oxhat, *orstd, *q, *oz, *ox, *hx, *eps;
+  float *dX = nullptr, *dPb = nullptr, *dY, *dXr;
+  // The BF16 path's node steps run launch by launch, with nX, Xb, dPb and the norms' arrays (nrm0, on,
+  // dnrm0, don) between them; the FP32 path's node tiles keep these in registers.  BF16: Pb, dD, dY + its
+  // gathered sum, and dT0 are read only by the next channel mixing, which rounds them to BF16, so
+  // their producers write them rounded, here (one at a time)
   __bf16 *mix16 = nullptr;
-  TA *dez2, *dez1, *dn0, *dnrm0, *dhz, *dox, *dq, *don;
+  TA *dez2, *dez1, *dn0, *dnrm0 = nullptr, *dhz, *dox, *dq, *don = nullptr;
   float *gpair;
 };
 
@@ -62,7 +63,7 @@ void plan_fused(WsPlan &p, const tn_model *m, int64_t N, int64_t MP, const BoxIn
   w->f0 = p.take<float>(bf16 ? MP * 3 * F / 2 : MP * 3 * F);   // BF16 in the BF16 path
   w->Xr = p.take<float>(N * 9 * F);
   w->T0 = p.take<float>(N * 9 * F);
-  w->nrm0 = p.take<TA>(N * F);
+  if (bf16) w->nrm0 = p.take<TA>(N * F);
   w->xhat0 = p.take<TA>(N * F);
   w->rstd0 = p.take<TA>(N);
   w->n0 = p.take<TA>(N * F);
@@ -76,8 +77,10 @@ void plan_fused(WsPlan &p, const tn_model *m, int64_t N, int64_t MP, const BoxIn
     v.resize(L);
     for (int64_t l = 0; l < L; ++l) v[l] = p.take<float>(count);
   };
-  per_layer(w->nX, N * F);
-  per_layer(w->Xb, N * 9 * F);
+  if (bf16) {
+    per_layer(w->nX, N * F);
+    per_layer(w->Xb, N * 9 * F);
+  }
   per_layer(w->Y, N * 9 * F);
   // pre-activations per pair: row-major BF16 in the BF16 path; the FP32 kernels store z1 and z2
   // in whole 16-pair blocks
@@ -102,7 +105,7 @@ void plan_fused(WsPlan &p, const tn_model *m, int64_t N, int64_t MP, const BoxIn
     w->Y16.resize(L);
     for (int64_t l = 0; l < L; ++l) w->Y16[l] = p.take<__bf16>(N * 9 * F);
   }
-  w->on = p.take<TA>(N * 3 * F);
+  if (bf16) w->on = p.take<TA>(N * 3 * F);
   w->oxhat = p.take<TA>(N * 3 * F);
   w->orstd = p.take<TA>(N);
   w->q = p.take<TA>(N * 3 * F);
@@ -117,19 +120,17 @@ void plan_fused(WsPlan &p, const tn_model *m, int64_t N, int64_t MP, const BoxIn
     for (int64_t l = 0; l < L; ++l) w->dM16[l] = p.take<__bf16>(N * 9 * F);
   }
   w->dX = p.take<float>(N * 9 * F);
-  w->dD = bf16 ? nullptr : p.take<float>(N * 9 * F);   // BF16: mix16
-  w->dPb = p.take<float>(N * 9 * F);
+  if (bf16) w->dPb = p.take<float>(N * 9 * F);
   w->dY = p.take<float>(N * 9 * F);
   w->dXr = p.take<float>(N * 9 * F);
-  w->dT0 = bf16 ? nullptr : p.take<float>(N * 9 * F);   // BF16: mix16
   w->dez2 = p.take<TA>(N * 3 * F);
   w->dez1 = p.take<TA>(N * 2 * F);
   w->dn0 = p.take<TA>(N * F);
-  w->dnrm0 = p.take<TA>(N * F);
+  if (bf16) w->dnrm0 = p.take<TA>(N * F);
   w->dhz = p.take<TA>(N * (F / 2));
   w->dox = p.take<TA>(N * F);
   w->dq = p.take<TA>(N * 3 * F);
-  w->don = p.take<TA>(N * 3 * F);
+  if (bf16) w->don = p.take<TA>(N * 3 * F);
   w->gpair = p.take<float>(3 * MP);
 }
 

@@ -63,7 +63,13 @@ __host__ __device__ inline void plan_mol(WsPlan &p, int64_t F, int64_t L, int64_
   w->f0 = p.take<float>(std::is_same<TA, float>::value ? MP * 3 * F / 2 : MP * 3 * F);   // BF16 in the BF16 path
   w->Xr = p.take<float>(N * 9 * F);
   w->T0 = p.take<float>(N * 9 * F);
-  w->nrm0 = p.take<TA>(N * F);
+  // (the FP32 path's node tiles keep in registers what the BF16 steps hand on in arrays)
+  constexpr bool bf16 = std::is_same<TA, float>::value;
+  auto steps = [&](auto *&x, int64_t count) {
+    using T = typename std::remove_reference<decltype(*x)>::type;
+    x = bf16 ? p.take<T>(count) : nullptr;
+  };
+  steps(w->nrm0, N * F);
   w->xhat0 = p.take<TA>(N * F);
   w->rstd0 = p.take<TA>(N);
   w->n0 = p.take<TA>(N * F);
@@ -73,8 +79,8 @@ __host__ __device__ inline void plan_mol(WsPlan &p, int64_t F, int64_t L, int64_
   w->g = p.take<TA>(N * 3 * F);
   for (int64_t l = 0; l <= L; ++l) w->X[l] = p.take<float>(N * 9 * F);
   for (int64_t l = 0; l < L; ++l) {
-    w->nX[l] = p.take<float>(N * F);
-    w->Xb[l] = p.take<float>(N * 9 * F);
+    steps(w->nX[l], N * F);
+    steps(w->Xb[l], N * 9 * F);
     w->Y[l] = p.take<float>(N * 9 * F);
     w->z1[l] = p.take<float>(MP * F);   // MP is a multiple of 16 (whole 16-pair blocks)
     w->z2[l] = p.take<float>(MP * 2 * F);
@@ -87,7 +93,7 @@ __host__ __device__ inline void plan_mol(WsPlan &p, int64_t F, int64_t L, int64_
     w->D[l] = p.take<float>(N * 9 * F);
     w->Y16[l] = std::is_same<TA, float>::value ? p.take<__bf16>(N * 9 * F) : nullptr;
   }
-  w->on = p.take<TA>(N * 3 * F);
+  steps(w->on, N * 3 * F);
   w->oxhat = p.take<TA>(N * 3 * F);
   w->orstd = p.take<TA>(N);
   w->q = p.take<TA>(N * 3 * F);
@@ -102,19 +108,19 @@ __host__ __device__ inline void plan_mol(WsPlan &p, int64_t F, int64_t L, int64_
     w->dM16[l] = std::is_same<TA, float>::value ? p.take<__bf16>(N * 9 * F) : nullptr;
   }
   w->dX = p.take<float>(N * 9 * F);
-  w->dD = p.take<float>(N * 9 * F);
-  w->dPb = p.take<float>(N * 9 * F);
+  steps(w->dD, N * 9 * F);
+  steps(w->dPb, N * 9 * F);
   w->dY = p.take<float>(N * 9 * F);
   w->dXr = p.take<float>(N * 9 * F);
-  w->dT0 = p.take<float>(N * 9 * F);
+  steps(w->dT0, N * 9 * F);
   w->dez2 = p.take<TA>(N * 3 * F);
   w->dez1 = p.take<TA>(N * 2 * F);
   w->dn0 = p.take<TA>(N * F);
-  w->dnrm0 = p.take<TA>(N * F);
+  steps(w->dnrm0, N * F);
   w->dhz = p.take<TA>(N * (F / 2));
   w->dox = p.take<TA>(N * F);
   w->dq = p.take<TA>(N * 3 * F);
-  w->don = p.take<TA>(N * 3 * F);
+  steps(w->don, N * 3 * F);
   w->gpair = p.take<float>(3 * MP);
 }
 
