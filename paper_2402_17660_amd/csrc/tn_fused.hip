@@ -40,7 +40,7 @@ struct FusedWs {
   NbrWs nb;
   float *geo, *phi, *f0, *Xr, *T0;
   TA *nrm0 = nullptr, *xhat0, *rstd0, *n0, *ez1, *ea1, *ez2, *g;
-  std::vector<float *> X, nX, Xb, Y, z1, z2, z3, h, M, P, nP, Pb, D, dM;
+  std::vector<float *> X, nX, Xb, Y, z1, z2, z3, M, P, nP, Pb, D, dM;
   std::vector<__bf16 *> Y16, dM16;   // BF16 copies of Y and dM for the gathers (BF16 path)
   TA *on = nullptr, *oxhat, *orstd, *q, *oz, *ox, *hx, *eps;
   float *dX = nullptr, *dPb = nullptr, *dY, *dXr;
@@ -89,7 +89,6 @@ void plan_fused(WsPlan &p, const tn_model *m, int64_t N, int64_t MP, const BoxIn
   per_layer(w->z2, bf16 ? MP * F : MP16 * 2 * F);
   per_layer(w->z3, bf16 ? MP * 3 * F / 2 : MP * 3 * F);
   // no h per pair: the message gathers form it from z3 and phi
-  w->h.assign(L, nullptr);
   per_layer(w->M, N * 9 * F);
   // P and ||P|| are formed again by the reverse pass (product_bwd_at), not stored
   w->P.assign(L, nullptr);
@@ -206,7 +205,6 @@ int run_fused(const tn_model *m, hipStream_t s, const Problem &pb, void *ws, siz
       pf.z1[l] = reinterpret_cast<__bf16 *>(w.z1[l]);
       pf.z2[l] = reinterpret_cast<__bf16 *>(w.z2[l]);
       pf.z3[l] = reinterpret_cast<__bf16 *>(w.z3[l]);
-      pf.h[l] = nullptr;   // not stored: the message gathers form it from z3 and phi
     }
     pf.geo = w.geo;
     pf.phi = w.phi;

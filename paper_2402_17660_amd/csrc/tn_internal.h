@@ -255,7 +255,7 @@ void split_args(const tn_model *m, PairBwdArgs &b);
 int launch_pair_fwd(hipStream_t s, int F, int K, const PairFwdArgs &a, int variant);
 int launch_pair_bwd(hipStream_t s, int F, int K, const PairBwdArgs &a, int variant);
 
-// BF16-operand variants: weights, stored pre-activations and (when stored) the edge filters h in BF16;
+// BF16-operand variants: weights and stored pre-activations in BF16;
 // biases, basis constants, f0 and every other stored quantity in FP32/FP64 as above.
 struct PairFwdArgsB {
   const int32_t *pairs = nullptr;
@@ -273,7 +273,6 @@ struct PairFwdArgsB {
   float *geo = nullptr, *phi = nullptr;
   __bf16 *f0 = nullptr;   // the embedding map W0 e + b0 in BF16
   __bf16 *z1[kMaxLayers], *z2[kMaxLayers], *z3[kMaxLayers];
-  __bf16 *h[kMaxLayers];   // the edge filters in BF16, or null: not stored (formed from z3 by the gathers)
 };
 
 struct PairBwdArgsB {

@@ -36,7 +36,7 @@ struct MolWs {
   float *geo, *phi, *f0, *Xr, *T0;
   TA *nrm0, *xhat0, *rstd0, *n0, *ez1, *ea1, *ez2, *g;
   float *X[kMaxLayers + 1], *nX[kMaxLayers], *Xb[kMaxLayers], *Y[kMaxLayers], *z1[kMaxLayers], *z2[kMaxLayers],
-      *z3[kMaxLayers], *h[kMaxLayers], *M[kMaxLayers], *P[kMaxLayers], *nP[kMaxLayers], *Pb[kMaxLayers],
+      *z3[kMaxLayers], *M[kMaxLayers], *P[kMaxLayers], *nP[kMaxLayers], *Pb[kMaxLayers],
       *D[kMaxLayers], *dM[kMaxLayers];
   __bf16 *Y16[kMaxLayers], *dM16[kMaxLayers];   // BF16 copies of Y and dM for the gathers (BF16 path)
   TA *on, *oxhat, *orstd, *q, *oz, *ox, *hz, *hx, *eps;
@@ -85,7 +85,6 @@ __host__ __device__ inline void plan_mol(WsPlan &p, int64_t F, int64_t L, int64_
     w->z1[l] = p.take<float>(MP * F);   // MP is a multiple of 16 (whole 16-pair blocks)
     w->z2[l] = p.take<float>(MP * 2 * F);
     w->z3[l] = p.take<float>(MP * 3 * F);
-    w->h[l] = nullptr;   // not stored (formed from z3 and phi where needed)
     w->M[l] = p.take<float>(N * 9 * F);
     w->P[l] = nullptr;   // formed again by the reverse pass, as in the fused path
     w->nP[l] = nullptr;
@@ -323,7 +322,6 @@ __global__ void __launch_bounds__(kMolThreads) k_mol_setup(MolCall c) {
     a->pfb.z1[l] = reinterpret_cast<__bf16 *>(w.z1[l]);
     a->pfb.z2[l] = reinterpret_cast<__bf16 *>(w.z2[l]);
     a->pfb.z3[l] = reinterpret_cast<__bf16 *>(w.z3[l]);
-    a->pfb.h[l] = nullptr;   // not stored: the message gathers form h from z3 and phi
     a->pbb.z1[l] = reinterpret_cast<const __bf16 *>(w.z1[l]);
     a->pbb.z2[l] = reinterpret_cast<const __bf16 *>(w.z2[l]);
     a->pbb.z3[l] = reinterpret_cast<const __bf16 *>(w.z3[l]);

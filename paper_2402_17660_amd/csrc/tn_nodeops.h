@@ -808,7 +808,7 @@ inline int mix(hipStream_t s, const T *in, T *out, int64_t N, int64_t F, const T
 
 // BF16 per-part channel mixing of [N, 9, F] features (see mix), FP32 or already rounded to BF16
 // (TI, the same results): Bt[p] is W_p (forward) or its transpose (adjoint), BF16, 16-byte
-// aligned.  F in {64, 128, 256}.
+// aligned.  F in {64, 128}.
 template <class TI>
 inline int mix_bf16(hipStream_t s, const TI *in, float *out, int64_t N, int64_t F, const __bf16 *const Bt[3],
                     int accumulate, __bf16 *out16 = nullptr) {
@@ -824,7 +824,6 @@ inline int mix_bf16(hipStream_t s, const TI *in, float *out, int64_t N, int64_t 
   if (F == 128)
     return pipe ? launch_mix_pipe<128, 2, true, TI>(s, in, out, N, Bv, accumulate, out16)
                 : launch_mix_bf16<128, TI>(s, in, out, N, Bt, accumulate, out16);
-  if (F == 256) return launch_mix_bf16<256, TI>(s, in, out, N, Bt, accumulate, out16);
   return TN_E_UNSUPPORTED;
 }
 
@@ -2149,8 +2148,7 @@ __global__ void __launch_bounds__(256) k_force_gather_w(int64_t n, const int32_t
                            gpair, forces);
 }
 
-// The embedding gather: F = 64 one wave per atom; F = 128 and 256 two waves per atom with
-// V = F/128 channels per lane; f0 in FP32 or BF16 (TF).
+// The embedding gather: F = 64 one wave per atom; F = 128 two waves per atom; f0 in FP32 or BF16 (TF).
 template <class TF, class TU>
 inline int embed_gather_w(hipStream_t s, int64_t F, int64_t n, const int32_t *rowptr, const int32_t *nbr,
                           const int32_t *pid, const int64_t *n_pairs, int64_t max_pairs, const int32_t *z, int max_z,
@@ -2166,8 +2164,6 @@ inline int embed_gather_w(hipStream_t s, int64_t F, int64_t n, const int32_t *ro
     TN_EMBED_LAUNCH(2, 1)
   else if (F == 128)
     TN_EMBED_LAUNCH(1, 2)
-  else if (F == 256)
-    TN_EMBED_LAUNCH(2, 2)
   else
     return TN_E_UNSUPPORTED;
 #undef TN_EMBED_LAUNCH
@@ -2180,15 +2176,10 @@ inline int embed_gather_w(hipStream_t s, int64_t F, int64_t n, const int32_t *ro
 // wave per atom, two channels per lane, so each load moves 4 bytes instead of 2 (on 100k
 // atoms 1.51 / 1.28 ms per launch against 1.65 / 1.45; for FP32 rows the same shape is 1.3 ms
 // per step slower).  Each channel's sum runs over the same edges in the same order either way.
-// hphi: when given, h holds z3 and the kernels form phi silu(z3) themselves.
+// h holds z3, hphi phi: the kernels form phi silu(z3) themselves.
 #define TN_MESSAGE_LAUNCH_HZ(KERNEL, VV, GG)                                                               \
-  if (hphi) {                                                                                              \
-    hipLaunchKernelGGL((KERNEL<VV, GG, TH, TY, TO, true>), dim3(wave_atom_grid(GG * n)), dim3(256), 0, s,   \
-                       n, rowptr, nbr, pid, n_pairs, max_pairs, h, hphi, y, o, a...);                      \
-  } else {                                                                                                 \
-    hipLaunchKernelGGL((KERNEL<VV, GG, TH, TY, TO, false>), dim3(wave_atom_grid(GG * n)), dim3(256), 0, s,  \
-                       n, rowptr, nbr, pid, n_pairs, max_pairs, h, hphi, y, o, a...);                      \
-  }
+  hipLaunchKernelGGL((KERNEL<VV, GG, TH, TY, TO, true>), dim3(wave_atom_grid(GG * n)), dim3(256), 0, s, n,  \
+                     rowptr, nbr, pid, n_pairs, max_pairs, h, hphi, y, o, a...);
 #define TN_MESSAGE_LAUNCHER(NAME, KERNEL)                                                                   \
   template <class TH, class TY, class TO, class... A>                                                     \
   inline int NAME(hipStream_t s, int64_t F, int64_t n, const int32_t *rowptr, const int32_t *nbr,          \
@@ -2201,8 +2192,6 @@ inline int embed_gather_w(hipStream_t s, int64_t F, int64_t n, const int32_t *ro
       TN_MESSAGE_LAUNCH_HZ(KERNEL, 2, 1)                                                \
     } else if (F == 128) {                                                                                 \
       TN_MESSAGE_LAUNCH_HZ(KERNEL, 1, 2)                                            \
-    } else if (F == 256) {                                                                                 \
-      TN_MESSAGE_LAUNCH_HZ(KERNEL, 2, 2)                                            \
     } else {                                                                                               \
       return TN_E_UNSUPPORTED;                                                                             \
     }                                                                                                      \

@@ -5,7 +5,7 @@
 // evaluated once per unordered pair, in one pass over pair tiles:
 //   forward   geometry + basis (FP64) -> f0 = W0 e + b0 -> per layer
 //             z1 = Wa e + ba, z2 = Wb silu(z1) + bb, z3 = Wc silu(z2) + bc, h = phi silu(z3)
-//             (the message gathers form h from z3; the BF16 kernel stores it when asked for)
+//             (h is not stored: the message gathers form it from z3)
 //   reverse   dE/df0, dE/dphi, dE/dvhat of the embedding and, per layer, dh from the two
 //             atoms' adjoint rows (gathered in the tile's prologue), then per layer
 //             dz3 = dh phi silu'(z3), dz2 = (dz3 Wc) silu'(z2), dz1 = (dz2 Wb) silu'(z1),
@@ -64,9 +64,6 @@ __device__ __forceinline__ void load_cols_t(const float *v, int col0, floatx4 (&
     for (int t = 0; t < 4; ++t) o[cb][t] = v[c + cb * 16 + t];
 }
 
-__device__ __forceinline__ floatx4 silu4(const floatx4 &z) {
-  return floatx4{fast_silu(z[0]), fast_silu(z[1]), fast_silu(z[2]), fast_silu(z[3])};
-}
 __device__ __forceinline__ floatx4 silu_and_grad4(const floatx4 &z, floatx4 &g) {
   floatx4 o;
 #pragma unroll
@@ -886,8 +883,7 @@ __global__ void __launch_bounds__(64 * NW, MINB) k_pair_bwd(PairBwdArgs a) {
 // GEMM operands (basis, activations, adjoints and weights) in BF16, FP32 accumulation
 // (v_mfma_f32_16x16x32_bf16: lane l holds A[l%16][8(l/16)..8(l/16)+7] and
 // B[8(l/16)..+7][l%16]).  Tiles of 16 RB pairs (RB 16-row blocks), so every weight fragment
-// read from L2 feeds RB MFMAs.  Pre-activations (and, when asked for, the filters h) are stored
-// in BF16.
+// read from L2 feeds RB MFMAs.  Pre-activations are stored in BF16.
 
 // acc[rb][cb] += act[16*RB x Kin] (LDS bf16, row stride ld) * Bt^T (Bt [ncol][Kin] bf16 in global
 // memory); with TR the operands of each instruction are swapped and the accumulator holds the
@@ -1014,13 +1010,9 @@ __device__ __forceinline__ void pair_fwd_tile_bf16(const PairFwdArgsB &a, int64_
       floatx4 br[NB];
       load_cols_t<NB>(a.bc[l], col0, br);
       wave_mm_bf16<RB, NB, true>(sA2, L2, 2 * F, a.Wc[l], col0, acc);
-      __bf16 *z3 = a.z3[l], *h = a.h[l];   // h only when given (see pair_fwd_tile)
+      __bf16 *z3 = a.z3[l];
       for_acc_t(acc, col0, [&](int, int cb, int row, int col, floatx4 &v) {
-        if (row < nvalid) {
-          v += br[cb];
-          st4(z3 + (p0 + row) * 3 * F + col, v);
-          if (h) st4(h + (p0 + row) * 3 * F + col, (float)sPhi[row] * silu4(v));
-        }
+        if (row < nvalid) st4(z3 + (p0 + row) * 3 * F + col, v + br[cb]);
       });
     }
   }
