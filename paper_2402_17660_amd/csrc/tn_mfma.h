@@ -90,21 +90,33 @@ __device__ __forceinline__ Frag3 ld_frag3(const __bf16 *p, int plane) {
                *reinterpret_cast<const bf16x8 *>(p + 2 * plane)};
 }
 
-// acc[n] += w[n] a for the N weight fragments w: the six products, smallest first, each over all n.
-template <int N>
-__device__ __forceinline__ void mfma_split(const Frag3 (&w)[N], const Frag3 &a, floatx4 (&acc)[N]) {
+// t[n] += W(n) A(n) over one chunk of 32 along K: the six products, smallest first.  The N chains are
+// independent; each instruction of a chain waits for the one before.
+template <int N, class FW, class FA>
+__device__ __forceinline__ void mfma_split(FW &&W, FA &&A, floatx4 (&t)[N]) {
 #pragma unroll
-  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].l, a.h, acc[n]);
+  for (int n = 0; n < N; ++n) t[n] = mfma_bf16(W(n).l, A(n).h, t[n]);
 #pragma unroll
-  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].h, a.l, acc[n]);
+  for (int n = 0; n < N; ++n) t[n] = mfma_bf16(W(n).h, A(n).l, t[n]);
 #pragma unroll
-  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].m, a.m, acc[n]);
+  for (int n = 0; n < N; ++n) t[n] = mfma_bf16(W(n).m, A(n).m, t[n]);
 #pragma unroll
-  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].m, a.h, acc[n]);
+  for (int n = 0; n < N; ++n) t[n] = mfma_bf16(W(n).m, A(n).h, t[n]);
 #pragma unroll
-  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].h, a.m, acc[n]);
+  for (int n = 0; n < N; ++n) t[n] = mfma_bf16(W(n).h, A(n).m, t[n]);
 #pragma unroll
-  for (int n = 0; n < N; ++n) acc[n] = mfma_bf16(w[n].h, a.h, acc[n]);
+  for (int n = 0; n < N; ++n) t[n] = mfma_bf16(W(n).h, A(n).h, t[n]);
+}
+// The same from zero: added to a running sum afterwards, a chunk rounds that once (its instructions would six
+// times, FP32 ones eight).  Used where it costs nothing: the channel mixings, and dE/de in the reverse pair
+// kernel, whose sums run over all channels.  Against 64 bits (600 atoms, F = 128, two layers) forces 6.6e-7 ->
+// 3.6e-7, energies of 22 atoms without layers 1.8e-8 -> 8.2e-9 an atom; in the pair kernels' other products
+// it changes neither and takes 3 to 15 % of their time.
+template <int N, class FW, class FA>
+__device__ __forceinline__ void mfma_split_zero(FW &&W, FA &&A, floatx4 (&t)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) t[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+  mfma_split(W, A, t);
 }
 
 // This wave's weights of a product in KC chunks of 32 along K: column blocks cb0 .. cb0 + NB - 1, packed by
@@ -131,8 +143,10 @@ struct SplitWeights {
 // acc[rb][cb] += act_rb * Bt^T from split operands: row i of the activations starts at act + i*ld
 // (LDS, h; m and l `plane` and 2 `plane` elements further).  The weights are the instruction's first
 // operand: entry t of acc[rb][cb] in lane l is D[rb*16 + l%16][(cb0 + cb)*16 + 4(l/16) + t].
-// The weights of the next PD chunks are in flight while the current chunk's products run.
-template <int RB, int NB, int KC, int PD>
+// The weights of the next PD chunks are in flight while the current chunk's products run.  SUMS: every chunk is
+// summed from zero and then added; otherwise the products go straight to acc, which spares the partial sums'
+// registers and additions.
+template <bool SUMS, int RB, int NB, int KC, int PD>
 __device__ __forceinline__ void wave_mm_split(const __bf16 *act, int plane, int ld, SplitWeights<NB, KC, PD> &B,
                                               floatx4 (&acc)[RB][NB]) {
   const int lane = threadIdx.x & 63;
@@ -143,7 +157,19 @@ __device__ __forceinline__ void wave_mm_split(const __bf16 *act, int plane, int 
     for (int cb = 0; cb < NB; ++cb) w[cb] = f[cb];
     if (kc + PD < KC) B.load(kc + PD, f);
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) mfma_split(w, ld_frag3(ap + rb * 16 * ld + 32 * kc, plane), acc[rb]);
+    for (int rb = 0; rb < RB; ++rb) {
+      const Frag3 a = ld_frag3(ap + rb * 16 * ld + 32 * kc, plane);
+      auto W = [&](int n) -> const Frag3 & { return w[n]; };
+      auto A = [&](int) -> const Frag3 & { return a; };
+      if constexpr (SUMS) {
+        floatx4 t[NB];
+        mfma_split_zero(W, A, t);
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) acc[rb][cb] += t[cb];
+      } else {
+        mfma_split(W, A, acc[rb]);
+      }
+    }
   };
   if constexpr (PD == 1) {
     for (int kc = 0; kc < KC; ++kc) chunk(kc, B.next[0]);

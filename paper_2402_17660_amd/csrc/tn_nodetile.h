@@ -212,6 +212,7 @@ struct NodeTile {
   static_assert(F % (16 * NW) == 0 && F % 32 == 0, "whole blocks per wave");
   static constexpr size_t bytes = 3 * PL * sizeof(__bf16) + 2 * F * sizeof(double);
   static constexpr int TA = 16, VT = 4;   // atoms; channels of a lane in a block
+  static constexpr int CG = NB == 1 ? 3 : 1;   // coordinates whose products run side by side
   static constexpr bool kEarly = false;
   using Feat = floatx4[9][NB];
   struct Frags {};
@@ -292,7 +293,9 @@ struct NodeTile {
     for (int c = 0; c < 9; ++c)
 #pragma unroll
       for (int cb = 0; cb < NB; ++cb) y[c][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
+    // (two blocks per wave, in the molecule kernel: unrolled, the chunks' loads fill registers and it spills)
+    constexpr int kUnroll = NB > 1 ? 1 : KC;
+#pragma unroll kUnroll
     for (int kc = 0; kc < KC; ++kc) {
       Frag3 w[3][NB];
 #pragma unroll
@@ -301,7 +304,16 @@ struct NodeTile {
         for (int cb = 0; cb < NB; ++cb) w[p][cb] = next[p][cb];
       if (kc + 1 < KC) weights(kc + 1);
 #pragma unroll
-      for (int c = 0; c < 9; ++c) mfma_split(w[coord_part(c)], ld_frag3(ap + c * 16 * LD + 32 * kc, PL), y[c]);
+      for (int c0 = 0; c0 < 9; c0 += CG) {   // two or three chains side by side
+        Frag3 a[CG];
+#pragma unroll
+        for (int n = 0; n < CG; ++n) a[n] = ld_frag3(ap + (c0 + n) * 16 * LD + 32 * kc, PL);
+        floatx4 t[CG * NB];
+        mfma_split_zero([&](int n) -> const Frag3 & { return w[coord_part(c0 + n / NB)][n % NB]; },
+                        [&](int n) -> const Frag3 & { return a[n / NB]; }, t);
+#pragma unroll
+        for (int n = 0; n < CG * NB; ++n) y[c0 + n / NB][n % NB] += t[n];
+      }
     }
   }
 };
@@ -384,19 +396,22 @@ struct NodeTileSmall {
   __device__ __forceinline__ void product(const MixSplit &, const Frags &f, Feat &y) const {
     const int r16 = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
     const __bf16 *ap = sA + r16 * LD + 8 * q;
-    floatx4 acc[4][1];
+    floatx4 acc[4];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) acc[rb][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < 4; ++rb) acc[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
+      Frag3 a[4];
+      floatx4 t[4];
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        const Frag3 w[1] = {f.w[kc][rb < 2 ? rb : 2]};
-        mfma_split(w, ld_frag3(ap + rb * 16 * LD + 32 * kc, PL), acc[rb]);
-      }
+      for (int rb = 0; rb < 4; ++rb) a[rb] = ld_frag3(ap + rb * 16 * LD + 32 * kc, PL);
+      mfma_split_zero([&](int rb) -> const Frag3 & { return f.w[kc][rb < 2 ? rb : 2]; },
+                 [&](int rb) -> const Frag3 & { return a[rb]; }, t);
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) acc[rb] += t[rb];
     }
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) st4(sY + (rb * 16 + r16) * LDY + wave * 16 + 4 * q, acc[rb][0]);
+    for (int rb = 0; rb < 4; ++rb) st4(sY + (rb * 16 + r16) * LDY + wave * 16 + 4 * q, acc[rb]);
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 9; ++c) y[c][0][0] = sY[at(c) * LDY + ch];

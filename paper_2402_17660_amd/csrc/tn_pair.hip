@@ -15,12 +15,12 @@ bool pair_kernels_support(int F, int K, int L, bool bf16) {
 // arithmetic in the same order, so results do not depend on the shape; tn_autotune picks the
 // fastest.  Pairs, waves and workgroups per CU, with the time of a launch on the 100,000-atom box
 // (2.6 M pairs) and on a 22-atom molecule (180 pairs; both F = 128, two layers):
-//   FP32 forward: 0 = 32, 8, 2 (9.1 ms, 37 us); 1 = 48, 4, 2 (8.3 ms, 53 us); 2 = 16, 8, 2 (13.0 ms, 26 us);
-//     3 = 16, 16, 1 with two chunks of weights in flight (16.3 ms, 26 us); 4 = 48, 8, 2 (8.4 ms, 47 us;
-//     F = 64: 32, 4, 3)
-//   FP32 reverse: 0 = 32, 4, 2 (14.5 ms, 66 us; F = 64: 48, 8, 2); 1 = 32, 8, 2 (14.6 ms, 60 us); 2 = 16, 8, 2
-//     (20.0 ms, 39 us); 3 = 16, 16, 1 with three chunks in flight (29.5 ms, 40 us); 4 = 64, 8, 1 (14.6 ms,
-//     88 us; F = 64: 32, 4, 2)
+//   FP32 forward: 0 = 32, 8, 2 (9.0 ms, 37 us); 1 = 48, 8, 2 (8.3 ms, 48 us; F = 64: 32, 4, 3); 2 = 16, 8, 2
+//     (12.9 ms, 27 us); 3 = 16, 16, 1 with two chunks of weights in flight (16.6 ms, 26 us); 4 = 48, 4, 2
+//     (8.5 ms, 56 us)
+//   FP32 reverse: 0 = 32, 4, 2 (14.6 ms, 65 us; F = 64: 48, 8, 2); 1 = 32, 8, 2 (14.9 ms, 59 us); 2 = 16, 8, 2
+//     (19.8 ms, 39 us); 3 = 16, 16, 1 with three chunks in flight (28.3 ms, 40 us); 4 = 64, 8, 1 (14.5 ms,
+//     87 us; F = 64: 32, 4, 2)
 //   BF16: 0 = 64 pairs, 4 waves, 1 per CU; 1 = 32, 4, 2; 2 = 48, 4, 2; 3, 4: below
 // With the products on FP32 instructions the best shapes took 13.7 and 18.7 ms, and 64 and 94 us.
 int pair_variant_count(bool bf16) { return bf16 ? 5 : 5; }
@@ -29,13 +29,13 @@ int pair_variant_count(bool bf16) { return bf16 ? 5 : 5; }
 // themselves are known on the device only; molecules fill about half of 32 pairs per atom, boxes
 // nearly all).  FP32: a budget of up to 1.5 tiles of 16 pairs per CU is a latency chain, one tile per CU
 // and most CUs idle: sixteen waves per tile share its rows and weight loads (166 atoms, 2700 pairs:
-// 28.9 and 46.1 us in shape 3, 28.1 and 48.3 in 2, 37 and 58 in the best of the others).  Up to 16384
+// 28.6 and 44.6 us in shape 3, 29.3 and 49.2 in 2, 36 and 58 in the best of the others).  Up to 16384
 // there are one or two tiles per CU, and the fewer waves of shape 2 let two of them share one
-// (400 atoms, 7500 pairs: 47 and 64 us, 57 and 96 in shape 3, 42 and 61 in the best of the others; F = 64
+// (400 atoms, 7500 pairs: 44 and 63 us, 58 and 91 in shape 3, 40 and 62 in the best of the others; F = 64
 // 22.6 and 31.3, 29 and 48, 23 and 36).  Beyond, the tile's reuse of each weight fragment and the waves
-// that hide its gathers decide, as at 2.6 M pairs: forward shape 1 (800 atoms, 20,900 pairs: 85 us, 96 in
-// 0 and 125 in 2; 6000 atoms 496, 552 in 0; F = 64 182, 225 in 0), reverse shape 1 (136 us, 144 in 0
-// and 183 in 2; 904 and 926 in 0), and shape 0 for F = 64 (343 us, 396 in 1; 800 atoms 54 and 68).
+// that hide its gathers decide, as at 2.6 M pairs: forward shape 1 (800 atoms, 20,900 pairs: 86 us, 96 in
+// 0 and 125 in 2; 6000 atoms 473, 539 in 0), reverse shape 1 (136 us, 144 in 0 and 183 in 2; 895 and 925 in
+// 0), and shape 0 for F = 64 (20,000 atoms 1142 us, 1233 in 1; 800 atoms 54 and 67).
 // BF16, forward and
 // reverse: 35 and 51 us in shape 1 at 180 pairs (38 and 75 in 0); 4.0 and 8.6 ms in shapes 4 and
 // 3 at 2.6 M pairs (5.6 and 12.1 in 0), shape 3 forward below 100,000 (132 against 145 us at
@@ -100,10 +100,10 @@ template <int F, int K>
 static int launch_fwd(hipStream_t s, const PairFwdArgs &a, int v) {
   constexpr bool wide = F == 128;
   switch (v) {
-    case 1: return launch_fwd_v<F, K, 3, 4, 2>(s, a);
+    case 1: return launch_fwd_v<F, K, wide ? 3 : 2, wide ? 8 : 4, wide ? 4 : 3>(s, a);
     case 2: return launch_fwd_v<F, K, 1, 8, 4>(s, a);
     case 3: return launch_fwd_v<F, K, 1, 16, 4, 2>(s, a);
-    case 4: return launch_fwd_v<F, K, wide ? 3 : 2, wide ? 8 : 4, wide ? 4 : 3>(s, a);
+    case 4: return launch_fwd_v<F, K, 3, 4, 2>(s, a);
     default: return launch_fwd_v<F, K, 2, 8, 4>(s, a);
   }
 }
@@ -116,7 +116,7 @@ static int launch_bwd(hipStream_t s, const PairBwdArgs &a, int v) {
     case 2: return launch_bwd_v<F, K, 1, 8, 4>(s, a);
     case 3: return launch_bwd_v<F, K, 1, 16, 4, 3>(s, a);
     case 4: return launch_bwd_v<F, K, wide ? 4 : 2, wide ? 8 : 4, 2>(s, a);
-    default: return launch_bwd_v<F, K, wide ? 2 : 3, wide ? 4 : 8, 2>(s, a);
+    default: return launch_bwd_v<F, K, wide ? 2 : 3, wide ? 4 : 8, wide ? 2 : 4>(s, a);
   }
 }
 

@@ -101,25 +101,25 @@ template <int RB, int NB>
 __device__ __forceinline__ void store_acc_blocks_t(float *z, int C, int64_t p0, int nvalid, int cb0,
                                                    const floatx4 (&acc)[RB][NB]) {
   const int lane = threadIdx.x & 63;
+  float *zt = z + (p0 / 16 * (C / 16) + cb0) * 256;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
     if (rb * 16 + (lane & 15) < nvalid) {
 #pragma unroll
-      for (int cb = 0; cb < NB; ++cb)
-        *reinterpret_cast<floatx4 *>(z + ((p0 / 16 + rb) * (C / 16) + cb0 + cb) * 256 + lane * 4) = acc[rb][cb];
+      for (int cb = 0; cb < NB; ++cb) st4(zt + (uint32_t)((rb * (C / 16) + cb) * 256 + lane * 4), acc[rb][cb]);
     }
 }
 template <int RB, int NB>
 __device__ __forceinline__ void load_acc_blocks_t(const float *z, int C, int64_t p0, int nvalid, int cb0,
                                                   floatx4 (&o)[RB][NB]) {
   const int lane = threadIdx.x & 63;
+  const float *zt = z + (p0 / 16 * (C / 16) + cb0) * 256;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb) {
       o[rb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-      if (rb * 16 < nvalid)
-        o[rb][cb] = *reinterpret_cast<const floatx4 *>(z + ((p0 / 16 + rb) * (C / 16) + cb0 + cb) * 256 + lane * 4);
+      if (rb * 16 < nvalid) o[rb][cb] = ld4(zt + (uint32_t)((rb * (C / 16) + cb) * 256 + lane * 4));
     }
 }
 
@@ -271,12 +271,21 @@ __device__ __forceinline__ void pair_fwd_tile(const PairFwdArgs &a, int64_t p0, 
   using Wa = SplitWeights<C1::NB, KP / 32, PD>;
   using Wb = SplitWeights<C2::NB, F / 32, PD>;
   using Wc = SplitWeights<C3::NB, 2 * F / 32, PD>;
-  // bias, SiLU and its derivative of one product's accumulator: silu to sA, silu' to z
-  auto activation = [&](auto cols, auto &acc, const auto &br, int ld, float *z, int zc) {
+  // the accumulators start from the biases (no registers for those during the product)
+  auto start = [&](const float *b, auto cols, auto &acc) {
     using C = decltype(cols);
-    for_acc_t(acc, C::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
+    load_cols_t<C::NB>(b, C::col0(wave), acc[0]);
+#pragma unroll
+    for (int rb = 1; rb < RB; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < C::NB; ++cb) acc[rb][cb] = acc[0][cb];
+  };
+  // SiLU and its derivative of one product's accumulator: silu to sA, silu' to z
+  auto activation = [&](auto cols, auto &acc, int ld, float *z, int zc) {
+    using C = decltype(cols);
+    for_acc_t(acc, C::col0(wave), [&](int, int, int row, int col, floatx4 &v) {
       floatx4 g;
-      st4_split(sA + row * ld + col, TILE * ld, silu_and_grad4(v + br[cb], g));
+      st4_split(sA + row * ld + col, TILE * ld, silu_and_grad4(v, g));
       v = g;   // all the reverse pass needs of the pre-activation, so that is what is stored
     });
     store_acc_blocks_t<RB, C::NB>(z, zc, p0, nvalid, C::cb0(wave), acc);
@@ -285,12 +294,13 @@ __device__ __forceinline__ void pair_fwd_tile(const PairFwdArgs &a, int64_t p0, 
   if (C3::on(wave)) {
     floatx4 acc[RB][C3::NB], br[C3::NB], bl[C3::NB];
     zero_acc_rb<RB, C3::NB>(acc);
+    wave_mm_split<false>(sE, TILE * LE, LE, w0, acc);
     // b0 to more than FP32: its rounding would be the same in every pair
     load_cols_t<C3::NB>(a.b0, C3::col0(wave), br);
     load_cols_t<C3::NB>(a.b0lo, C3::col0(wave), bl);
-    wave_mm_split(sE, TILE * LE, LE, w0, acc);
+    float *f0 = a.f0 + p0 * 3 * F;   // (the tile's rows by 32-bit offsets: 64-bit addresses would fill registers)
     for_acc_t(acc, C3::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
-      if (row < nvalid) st4(a.f0 + (p0 + row) * 3 * F + col, (v + bl[cb]) + br[cb]);
+      if (row < nvalid) st4(f0 + (uint32_t)(row * 3 * F + col), (v + bl[cb]) + br[cb]);
     });
   }
   for (int l = 0; l < a.L; ++l) {
@@ -301,36 +311,33 @@ __device__ __forceinline__ void pair_fwd_tile(const PairFwdArgs &a, int64_t p0, 
       __syncthreads();
     }
     // z1 = Wa e + ba
-    floatx4 acc1[RB][C1::NB], br1[C1::NB];
+    floatx4 acc1[RB][C1::NB];
     if (C1::on(wave)) {
-      zero_acc_rb<RB, C1::NB>(acc1);
-      load_cols_t<C1::NB>(a.ba[l], C1::col0(wave), br1);
-      wave_mm_split(sE, TILE * LE, LE, wa, acc1);
+      start(a.ba[l], C1(), acc1);
+      wave_mm_split<false>(sE, TILE * LE, LE, wa, acc1);
     }
     Wb wb(a.Wb[l], first(C2()));
     __syncthreads();   // every wave has read e (and, with e apart, the previous layer's silu(z2))
-    if (C1::on(wave)) activation(C1(), acc1, br1, L1, a.z1[l], F);
+    if (C1::on(wave)) activation(C1(), acc1, L1, a.z1[l], F);
     __syncthreads();
     // z2 = Wb silu(z1) + bb
-    floatx4 acc2[RB][C2::NB], br2[C2::NB];
+    floatx4 acc2[RB][C2::NB];
     if (C2::on(wave)) {
-      zero_acc_rb<RB, C2::NB>(acc2);
-      load_cols_t<C2::NB>(a.bb[l], C2::col0(wave), br2);
-      wave_mm_split(sA, TILE * L1, L1, wb, acc2);
+      start(a.bb[l], C2(), acc2);
+      wave_mm_split<false>(sA, TILE * L1, L1, wb, acc2);
     }
     Wc wc(a.Wc[l], first(C3()));
     __syncthreads();
-    if (C2::on(wave)) activation(C2(), acc2, br2, L2, a.z2[l], 2 * F);
+    if (C2::on(wave)) activation(C2(), acc2, L2, a.z2[l], 2 * F);
     __syncthreads();
     // z3 = Wc silu(z2) + bc
     if (C3::on(wave)) {
-      floatx4 acc[RB][C3::NB], br[C3::NB];
-      zero_acc_rb<RB, C3::NB>(acc);
-      load_cols_t<C3::NB>(a.bc[l], C3::col0(wave), br);
-      wave_mm_split(sA, TILE * L2, L2, wc, acc);
-      float *z3 = a.z3[l];
-      for_acc_t(acc, C3::col0(wave), [&](int, int cb, int row, int col, floatx4 &v) {
-        if (row < nvalid) st4(z3 + (p0 + row) * 3 * F + col, v + br[cb]);
+      floatx4 acc[RB][C3::NB];
+      start(a.bc[l], C3(), acc);
+      wave_mm_split<false>(sA, TILE * L2, L2, wc, acc);
+      float *z3 = a.z3[l] + p0 * 3 * F;
+      for_acc_t(acc, C3::col0(wave), [&](int, int, int row, int col, floatx4 &v) {
+        if (row < nvalid) st4(z3 + (uint32_t)(row * 3 * F + col), v);
       });
     }
   }
@@ -795,7 +802,7 @@ __device__ __forceinline__ void pair_bwd_tile(const PairBwdArgs &a, int64_t p0, 
       const int c = wave + NW * n;
       if (c < RB * KB) {
         SplitWeights<1, decltype(kc)::value, PD> w(Bt, c % KB);
-        wave_mm_split(sG + (c / KB) * 16 * ld, TILE * ld, ld, w, de[n]);
+        wave_mm_split<true>(sG + (c / KB) * 16 * ld, TILE * ld, ld, w, de[n]);
       }
     }
   };
@@ -824,7 +831,7 @@ __device__ __forceinline__ void pair_bwd_tile(const PairBwdArgs &a, int64_t p0, 
     if (C2::on(wave)) {
       zero_acc_rb<RB, C2::NB>(acc2);
       load_acc_blocks_t<RB, C2::NB>(a.z2[l], 2 * F, p0, nvalid, C2::cb0(wave), zp2);
-      wave_mm_split(sG, TILE * L3, L3, wc, acc2);
+      wave_mm_split<false>(sG, TILE * L3, L3, wc, acc2);
     }
     SplitWeights<C1::NB, 2 * F / 32, PD> wb(a.WbT[l], C1::cb0(C1::on(wave) ? wave : 0));
     __syncthreads();
@@ -835,7 +842,7 @@ __device__ __forceinline__ void pair_bwd_tile(const PairBwdArgs &a, int64_t p0, 
     if (C1::on(wave)) {
       zero_acc_rb<RB, C1::NB>(acc1);
       load_acc_blocks_t<RB, C1::NB>(a.z1[l], F, p0, nvalid, C1::cb0(wave), zp1);
-      wave_mm_split(sG, TILE * L2, L2, wb, acc1);
+      wave_mm_split<false>(sG, TILE * L2, L2, wb, acc1);
     }
     __syncthreads();
     if (C1::on(wave)) gate(C1(), acc1, zp1, L1);
