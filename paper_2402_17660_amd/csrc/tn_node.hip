@@ -24,9 +24,10 @@ __global__ void __launch_bounds__(64 * NT::NW) k_node_bwd(NodeBwdArgs a) {
 }
 
 // Which tile: the small one while a compute unit gets at most two of them (four at F = 64, where they are
-// half as large).  The six launches of two layers, us, small and large tiles (256 compute units):
-// F = 128, 22 atoms 69 / 148, 800 86 / 162, 1400 163 / 173, 2000 180 / 192, 2489 243 / 192, 6000 485 / 384;
-// F = 64, 48 atoms 43 / 81, 1500 65 / 101, 3000 90 / 114, 4000 115 / 128.
+// half as large).  A call of energies and forces, two layers, us, small and large tiles (256 compute units):
+// F = 128, 22 atoms 281 / 370, 800 618 / 709, 1400 934 / 962, 2000 1163 / 1188, 2489 1440 / 1405, 4000 2121 / 2041;
+// F = 64, 48 atoms 195 / 251, 1500 433 / 479, 3000 711 / 743, 4000 886 / 911, 6000 1232 / 1262 (2 % behind the line,
+// where the large tile reads the weights a quarter as often).
 bool small_tiles(int F, int64_t N) { return N * F <= 2048 * 128; }
 
 }  // namespace

@@ -14,11 +14,11 @@
 //            W1^T mixing, normalisation adjoint, then the same of the layer below
 //            W1^T mixing, normalisation adjoint, gate adjoint, embedding mixing's adjoint
 // Bound by those reads and writes: for a 100,000-atom box at F = 128 and two layers 37 arrays of
-// 461 MB, 3.6 ms at the rate of a large copy; the six launches take 4.7 ms, one launch per step (61
+// 461 MB, 3.6 ms at the rate of a large copy; the six launches take 5.1 ms, one launch per step (61
 // arrays, ten of them mixings on FP32 instructions) 6.4 ms.  A large tile alone on its compute unit is
-// bound by its vector instructions and the memory-side cache's latency: 24 us on average for 22 atoms
+// bound by its vector instructions and the memory-side cache's latency: 27 us on average for 22 atoms
 // at F = 128, of which the maps and staging about half, the mixings' weights the rest; the small
-// tile takes 11.5 us (a call 370 -> 291 us).
+// tile takes 12.7 us (a call 370 -> 281 us).
 //
 // The mixings run on split operands (tn_mfma.h).
 #pragma once

@@ -274,7 +274,7 @@ __device__ __forceinline__ void st_dual4(Dual<float> *p, const Dual<float> (&o)[
 // current one's products.  The weights are the instruction's first operand: a lane ends with four
 // columns of one row, so the epilogue's dual arrays move 32 bytes per lane.  Bound by those arrays
 // (8 bytes a number, about 8 GB per step of 64 molecules at F = 128 and three layers, 1.7 ms at the rate of a
-// large copy) and by the products about alike: 4.1 -> 2.6 ms of that step.
+// large copy) and by the products about alike: 4.1 ms of that step on FP32 instructions, 2.8 ms here.
 template <int NB>
 __global__ void __launch_bounds__(256, 2) k_gemm_dual_split(DualGemmArgs<float> g) {
   using D = Dual<float>;
@@ -601,7 +601,7 @@ __global__ void __launch_bounds__(256) k_wgrad_mfma(const Dual<S> *A, RowMap ma,
 // thread stages eight rows of one column of A (and of B), so the loads run along the columns and the
 // operands lie in LDS by column, rows contiguous, as the instruction reads them.  The larger tile
 // reads A and B half as often, which with the partial sums' traffic is what the launch is bound by
-// (the step above: 2.8 -> 1.7 ms, the sums of the slices 0.58 -> 0.28 ms).
+// (the step above: 2.8 ms on FP32 instructions, 1.8 ms here, the sums of the slices 0.58 and 0.27 ms).
 template <int TO, int TK>
 __global__ void __launch_bounds__(4 * TO) k_wgrad_split(const Dual<float> *A, RowMap ma, const Dual<float> *B, RowMap mb,
                                                         int64_t R, const int64_t *Rdev, int O, int Kc, int64_t slice,
@@ -744,7 +744,7 @@ struct Reducer {
   // unit, two of the larger split tiles), at least 256 rows per slice (128), and the partial sums within the
   // scratch.  Fewer slices leave less to sum, more of them keep the chip busy when there are few rows
   // (the mixings'): split tiles per compute unit / least rows 1 / 256, 2 / 256, 2 / 128, 2 / 64, 4 / 32 of a
-  // 64-molecule step 10.6, 9.99, 9.77, 9.81, 9.88 ms.
+  // 64-molecule step 10.6, 9.99, 9.77, 9.81, 9.88 ms (with operand parts cut off, not rounded; now 10.0 at 2 / 128).
   int slices(int64_t R, int O, int Kc, int TO, int TK) const {
     const int64_t tiles = TO ? (int64_t)(O / TO) * (Kc / TK) : (int64_t)((O + 63) / 64) * ((Kc + 63) / 64);
     const int64_t want = TO ? 512 : 2048, rows = TO ? 128 : 256;
