@@ -48,7 +48,8 @@ __device__ __forceinline__ void st4(__bf16 *p, const floatx4 &v) {
 // sign and exponent range: h = bf16(x), m = bf16(x - h) and l = x - h - m, all rounded to nearest.
 // Both differences are exact, and l has the bits that are left of the 24 (|m| <= 2^-8 |x|, |l| <=
 // 2^-17 |x|), so h + m + l is x itself, with no scale to choose and whatever other entries its
-// matrix or row has (for |x| >= 2^-110; below, l ends at BF16's smallest number, 2^-133).  A product
+// matrix or row has (for |x| >= 2^-110; below, l ends at BF16's smallest number, 2^-133; and up to the
+// largest BF16 number, 2^128 - 2^120: h of the last FP32 numbers above it may be infinite).  A product
 // is the six largest of the nine BF16 products with FP32 accumulation; the three left out (m l, l m,
 // l l) are at most 2^-24 of it together, of either sign, and 2^-27.4 in RMS.  Six
 // v_mfma_f32_16x16x32_bf16 do the work of eight v_mfma_f32_16x16x4_f32 in 96 matrix cycles instead

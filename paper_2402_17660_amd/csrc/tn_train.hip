@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(256) k_gemm_dual(DualGemmArgs<S> g) {
 // ---------------------------------------------------------------- FP32 products as BF16 products
 // The products of tn_mfma.h's three BF16 parts: exact operands of any size (BF16 has FP32's exponents, so
 // adjoints need no scale), the six largest of nine BF16 products, FP32 accumulation.  Of an infinity the
-// remainders are NaN: a sum that comes out NaN is formed again from the operands themselves.
+// remainders are NaN: a sum that comes out NaN, of operands without one, is formed again from the operands themselves.
 constexpr int kPadT = 8;   // LDS row padding (elements)
 
 // c += a b: the five smaller products are summed by themselves, so that the sum's rounding is that of one
@@ -373,19 +373,32 @@ __global__ void __launch_bounds__(256, 2) k_gemm_dual_split(DualGemmArgs<float> 
       if (m >= Mrows) continue;
       D v[4], x[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < 4; ++t)
         v[t] = D(acc[0][a][b][t] + low[0][a][b][t], acc[1][a][b][t] + low[1][a][b][t]);
-        if (__builtin_expect(isnan(v[t].v) || isnan(v[t].d), 0)) {
-          v[t] = D(0.f, 0.f);
-          for (int64_t k = 0; k < g.K; ++k) {
-            const D x = A[m * g.lda + k];
-            const float w = g.transB ? B[(n + t) * g.ldb + k] : B[k * g.ldb + n + t];
-            v[t].v += x.v * w;
-            v[t].d += x.d * w;
+      bool open = false;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) open |= isnan(v[t].v) || isnan(v[t].d);
+      if (__builtin_expect(open, 0)) {
+        D s[4] = {D(0.f), D(0.f), D(0.f), D(0.f)};
+        for (int64_t k = 0; k < g.K && open; k += 4) {   // (four loads of each operand in flight)
+          open = false;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const D x = A[m * g.lda + k + e];
+              const float w = g.transB ? B[(n + t) * g.ldb + k + e] : B[(k + e) * g.ldb + n + t];
+              s[t].v += x.v * w;
+              s[t].d += x.d * w;
+            }
+            open |= (isnan(v[t].v) && !isnan(s[t].v)) || (isnan(v[t].d) && !isnan(s[t].d));
           }
         }
-        v[t].v += bias[t];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = D(isnan(v[t].v) ? s[t].v : v[t].v, isnan(v[t].d) ? s[t].d : v[t].d);
       }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t].v += bias[t];
       if (g.Z) st_dual4(g.Z + z * g.zoff + m * g.ldz + n, v);
       if (g.act == 1) {
 #pragma unroll
@@ -686,22 +699,67 @@ __global__ void __launch_bounds__(4 * TO) k_wgrad_split(const Dual<float> *A, Ro
     }
     __syncthreads();
   }
+  // entry (a, b, t) of this lane is bit 8 a + 4 b + t
+  auto entries = [&](auto &&f) {
+#pragma unroll
+    for (int a = 0; a < AO; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) f(a, b, t, 1u << (8 * a + 4 * b + t));
+  };
+  unsigned nan = 0;
+#pragma unroll
+  for (int a = 0; a < AO; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] += low[a][b];
+  entries([&](int a, int b, int t, unsigned bit) { nan |= isnan(acc[a][b][t]) ? bit : 0u; });
+  if (__syncthreads_or(nan != 0)) {   // infinities' NaN: those of columns without a NaN of their own
+    int *bad = reinterpret_cast<int *>(sA);
+    for (int t = tid; t < TO + TK; t += 4 * TO) bad[t] = 0;
+    __syncthreads();
+    auto scan = [&](const D *p, RowMap mp, int c0, int C, int *flag) {
+      const int c = tid % C, groups = 4 * TO / C;
+      bool found = false;
+#pragma unroll 4
+      for (int64_t r = rb + tid / C; r < re; r += groups) {
+        const D x = p[row_at(mp, r) + c0 + c];
+        found |= isnan(x.v) || isnan(x.d);
+      }
+      if (found) flag[c] = 1;
+    };
+    scan(A, ma, o0, TO, bad);
+    scan(B, mb, k0, TK, bad + TO);
+    __syncthreads();
+    entries([&](int a, int b, int t, unsigned bit) {
+      if (bad[wo + 16 * a + r16] | bad[TO + wk + 16 * b + 4 * q + t]) nan &= ~bit;
+    });
+    floatx4 s[AO][2];
+    zero_acc_rb<AO, 2>(s);
+    unsigned left = nan;
+    for (int64_t r = rb; r < re && left; ++r) {
+      D x[AO], y[2][4];
+#pragma unroll
+      for (int a = 0; a < AO; ++a) x[a] = A[row_at(ma, r) + o0 + wo + 16 * a + r16];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) y[b][t] = B[row_at(mb, r) + k0 + wk + 16 * b + 4 * q + t];
+      entries([&](int a, int b, int t, unsigned bit) {
+        s[a][b][t] += x[a].v * y[b][t].d + x[a].d * y[b][t].v;
+        if (isnan(s[a][b][t])) left &= ~bit;
+      });
+    }
+    entries([&](int a, int b, int t, unsigned bit) {
+      if (nan & bit) acc[a][b][t] = s[a][b][t];
+    });
+    __syncthreads();   // sA is free again
+  }
 #pragma unroll
   for (int a = 0; a < AO; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int o = o0 + wo + 16 * a + r16, k = k0 + wk + 16 * b + 4 * q;
-      acc[a][b] += low[a][b];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (__builtin_expect(isnan(acc[a][b][t]), 0)) {
-          float s = 0.f;
-          for (int64_t r = rb; r < re; ++r) {
-            const D x = A[row_at(ma, r) + o], y = B[row_at(mb, r) + k + t];
-            s += x.v * y.d + x.d * y.v;
-          }
-          acc[a][b][t] = s;
-        }
       const D v[4] = {D(0.f, acc[a][b][0]), D(0.f, acc[a][b][1]), D(0.f, acc[a][b][2]), D(0.f, acc[a][b][3])};
       st_dual4(P + ((int64_t)blockIdx.z * O + o) * Kc + k, v);
     }

@@ -5,10 +5,15 @@ Ragged shapes to the FP32 bars of the training tests and, over the whole gradien
 1.5e-6: the FP32 step is off by 3e-7 to 6e-7 (1.4e-6 for seven atoms whose terms cancel), and one of the six
 products left out would be an RMS error of 2^-18.6 (2.5e-6) of each of some ten products in a row."""
 
+import time
+
 import numpy as np
 import pytest
+import torch
 
-from tests.test_gpu_train import _case, _check, _gpu
+from paper_2402_17660_amd import TensorNet
+from tests.test_gpu_train import _case, _check, _gpu, _molecules
+from tests.util import small_blob
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +47,34 @@ def test_infinities_stay_what_they_are(dev, F, L):
     for k in ref:
         for kind in (np.isnan, np.isposinf, np.isneginf):
             assert np.array_equal(kind(got[k]), kind(ref[k])), (k, kind.__name__)
+
+
+def test_steps_with_nan_take_no_longer(dev):
+    """NaN and infinite targets: only sums of operands without a NaN are formed again, so the step takes about the time
+    of a finite one (within a factor of 3; with all of them formed again it was 18 and more)."""
+    pos, z, batch = _molecules(tuple(range(24, 120, 6)), 25)
+    S = int(batch[-1]) + 1
+    rng = np.random.default_rng(26)
+    E_ref, F_ref = rng.normal(size=S), rng.normal(size=pos.shape)
+    model = TensorNet(small_blob(F=128, K=32, L=3, seed=27), dev)
+    t = lambda a, dt: torch.tensor(a, dtype=dt, device=dev)
+
+    def ms(E, F):
+        args = (t(pos, torch.float32), t(z, torch.int32), t(batch, torch.int32), S, t(E, torch.float64),
+                t(F, torch.float64))
+        out = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            start = time.perf_counter()
+            model.train_grad(*args, precision="fp32", check=False)
+            torch.cuda.synchronize()
+            out.append(time.perf_counter() - start)
+        return 1e3 * sorted(out)[1]
+
+    finite = ms(E_ref, F_ref)
+    E_inf, E_nan, F_nan = E_ref.copy(), E_ref.copy(), np.full_like(F_ref, np.nan)
+    E_inf[3], E_nan[3] = np.inf, np.nan
+    for name, E, F in (("infinite energy", E_inf, F_ref), ("NaN energy", E_nan, F_ref), ("NaN forces", E_ref, F_nan)):
+        took = ms(E, F)
+        print(f"{name}: {took:.2f} ms, finite {finite:.2f} ms", flush=True)
+        assert took <= 3 * finite, name
